@@ -106,7 +106,7 @@ def kernel_sources_digest() -> str:
     import hashlib
     d = os.path.join(ROOT, "paper_1707_02423_amd", "csrc")
     h = hashlib.sha256()
-    for name in ("cfsim_internal.h", "pair_device.h", "pair.hip"):
+    for name in ("cfsim_internal.h", "pair_device.h", "pair_kernels.h", "pair.hip"):
         with open(os.path.join(d, name), "rb") as f:
             h.update(name.encode() + b"\0" + f.read())
     return h.hexdigest()

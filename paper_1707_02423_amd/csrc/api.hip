@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "cfsim_internal.h"
+#include "strip_job.h"
 
 // Device scratch of cfsim_score_noalloc: the workspace of cfsim_score, held
 // by every GPU the library runs on until the process ends.  In host code
@@ -431,7 +432,8 @@ cfsim_status cfsim_context_create(cfsim_context** out, int device) {
         delete ctx;
         return hip_fail(e, "hipDeviceGetAttribute");
     }
-    if ((e = cfsim::set_kernel_attributes()) != 0 || (e = cfsim::set_large_attributes()) != 0) {
+    if ((e = cfsim::set_kernel_attributes()) != 0 || (e = cfsim::set_large_attributes()) != 0 ||
+        (e = cfsim::set_strip_attributes()) != 0) {
         delete ctx;
         return hip_fail(e, "hipFuncSetAttribute");
     }
@@ -582,13 +584,22 @@ static int plain_variant(int nA, int nB, int nnzA, int nnzB, int esize, cfsim::P
     return first;
 }
 
+static size_t score_ws_min(int32_t n_a, int32_t n_b, const cfsim_options* opt) {
+    const size_t esize = fp64_final(opt) ? 8 : esize_of(opt->dtype);
+    // the two iterate buffers of the global kernel (the LDS kernels need none)
+    return align256(2 * (size_t)n_a * (size_t)n_b * esize);
+}
+
 size_t cfsim_score_workspace_size(const cfsim_context* ctx, int32_t n_a, int32_t n_b, const cfsim_options* opt) {
     (void)ctx;
     if (n_a < 1 || n_b < 1 || !opt) return 0;
     const size_t esize = fp64_final(opt) ? 8 : esize_of(opt->dtype);
     if (opt->resize == CFSIM_RESIZE_BILINEAR) return large_ws_bytes(1, n_a > n_b ? n_a : n_b, (int)esize, 6);
-    // the two iterate buffers of the global kernel (the LDS kernels need none)
-    return align256(2 * (size_t)n_a * (size_t)n_b * esize);
+    const size_t least = score_ws_min(n_a, n_b, opt);
+    if (least < ((size_t)64 << 10)) return least;  // always in LDS
+    // the strip path's lists and tables beside them
+    const size_t strips = align256(cfsim::strip_bytes(n_a, n_b, (int)esize));
+    return least > strips ? least : strips;
 }
 
 cfsim_status cfsim_score(cfsim_context* ctx, const cfsim_graph* A, const cfsim_graph* B, const cfsim_options* opt,
@@ -657,7 +668,7 @@ cfsim_status cfsim_score(cfsim_context* ctx, const cfsim_graph* A, const cfsim_g
     const int variant = plain_variant(A->n, B->n, A->nnz, B->nnz, esize, &sh);
     if (variant < 0)
         return fail(CFSIM_E_UNSUPPORTED, "pair %d x %d: its graph lists do not fit the kernels' LDS", B->n, A->n);
-    const size_t need = cfsim_score_workspace_size(ctx, A->n, B->n, opt);
+    const size_t need = score_ws_min(A->n, B->n, opt);
     if (ws_bytes < need || !ws) return fail(CFSIM_E_WORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, need);
     if (!ctx) return fail(CFSIM_E_INVALID_ARG, "context is NULL");
     // FP64 pass (near-tie FP32 result): the first FP64 kernel that holds the pair
@@ -682,7 +693,20 @@ cfsim_status cfsim_score(cfsim_context* ctx, const cfsim_graph* A, const cfsim_g
     int e = (int)hipSetDevice(ctx->device);
     if (e != 0) return hip_fail(e, "hipSetDevice");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    e = cfsim::launch_pair_lds(variant, opt->dtype, job, 1, st);
+    // A pair past LDS runs on strips (one launch per update over the whole
+    // chip) when the workspace holds their tables, as the workspace that
+    // cfsim_score_workspace_size names does; with less (the static scratch of
+    // cfsim_score_noalloc near its limit) in one workgroup.
+    const int largest = A->n > B->n ? A->n : B->n;
+    if (variant == cfsim::kBucketGlobal && largest <= cfsim::kStripMaxNodes && opt->max_iter <= cfsim::kStripMaxIter &&
+        ws_bytes >= cfsim::strip_bytes(A->n, B->n, esize)) {
+        cfsim::StripJob S{};
+        S.J = job;
+        cfsim::carve_strips(&S, ws, esize);
+        e = cfsim::launch_strips(opt->dtype, S, st);
+    } else {
+        e = cfsim::launch_pair_lds(variant, opt->dtype, job, 1, st);
+    }
     if (e != 0) return hip_fail(e, "pair kernel launch");
     if (variant64 >= 0) {  // runs only if the FP32 result is a near tie (decided on the device)
         job.refine = 1;
@@ -703,7 +727,8 @@ cfsim_status cfsim_score_noalloc(cfsim_context* ctx, const cfsim_graph* A, const
     if ((s = check_options(opt)) != CFSIM_OK) return s;
     if (!res) return fail(CFSIM_E_INVALID_ARG, "res is NULL");
     if (!ctx) return fail(CFSIM_E_INVALID_ARG, "context is NULL");
-    const size_t need = cfsim_score_workspace_size(ctx, A->n, B->n, opt);
+    const size_t need = opt->resize == CFSIM_RESIZE_BILINEAR ? cfsim_score_workspace_size(ctx, A->n, B->n, opt)
+                                                             : score_ws_min(A->n, B->n, opt);
     if (need > (size_t)CFSIM_NOALLOC_SCRATCH_BYTES)
         return fail(CFSIM_E_UNSUPPORTED, "pair %d x %d needs %zu bytes of scratch; the static scratch holds %zu",
                     B->n, A->n, need, (size_t)CFSIM_NOALLOC_SCRATCH_BYTES);

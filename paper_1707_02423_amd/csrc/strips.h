@@ -1,0 +1,318 @@
+// The update Y = B S A^T + B^T S A on strips of four rows of X = S^T, for
+// iterates in global memory (one workgroup per strip and launch).
+//
+// X has a row per node c of the C graph and a column per node i of the R
+// graph.  An entry of the update is
+//   Y[i][c] = sum_{u in succ(i)} w_iu P1[u] + sum_{u in pred(i)} w_ui P2[u],
+//   P1[u] = sum_{v in succ(c)} w_cv X[v][u],  P2[u] = sum_{v in pred(c)} w_vc X[v][u].
+// Stage A forms P1 and P2 of the strip's four rows: their source rows are
+// merged into one list (a strip's rows are consecutive nodes, which share
+// most neighbours), each read once, coalesced, and added to all four rows by
+// a matrix instruction (FP32: v_mfma_f32_4x4x1, an outer product of the four
+// weights with 64 columns; its terms round like fma, and a weight of zero
+// leaves a row unchanged).  Stage B gathers every column's neighbours from P1
+// and P2 in LDS, four rows per 16-byte read, at addresses from lists that are
+// laid out per column.  Nothing is gathered from global memory.  The terms of
+// an entry are added in the order of the gathers from S (inner over C's list,
+// outer over R's list), so the bits are the same.
+#pragma once
+
+#include "pair_device.h"
+
+namespace cfsim {
+namespace strips {
+
+constexpr int kRows = 4;           // rows of X per strip
+constexpr int kThreads = 512;      // workgroup of a strip
+constexpr int kWaves = kThreads / kWave;
+constexpr int kSrcS = 8;           // merged successor sources of a strip (4 rows, at most 2 each)
+constexpr int kSrcP = 16;          // merged predecessor sources (4 rows, at most 4 each)
+constexpr int kSrcFast = 8;        // predecessor sources whose reads are issued together
+
+// Sources of one strip: rows of X and the four rows' weights of each.
+template <typename T>
+struct alignas(16) StripTab {
+    T ws[kSrcS][kRows];
+    T wp[kSrcP][kRows];
+    int src_s[kSrcS], src_p[kSrcP];
+    int np;                        // predecessor sources past the fast ones are looped over
+    int long_rows;                 // bit r: row r has list entries past the slots
+    int pad[2];
+};
+
+// Lists of the columns (R nodes), one array per slot of `stride` entries:
+// byte offsets of the neighbours in P1 / P2 and weights; absent slots point at
+// the zero entry behind the last column, with weight 0.
+template <typename T>
+struct Cols {
+    const int* so;   // [2][stride]
+    const int* po;   // [4][stride]
+    const T* sw;
+    const T* pw;
+    int stride;
+};
+
+__host__ __device__ inline int col_stride(int nR) { return (nR + kWave - 1) / kWave * kWave; }
+template <typename T>
+__host__ __device__ inline size_t cols_bytes(int nR, int dp) {
+    return (size_t)col_stride(nR) * (2 + dp) * (sizeof(int) + sizeof(T));
+}
+template <typename T>
+__device__ inline Cols<T> carve_cols(unsigned char* base, int nR, int dp) {
+    Cols<T> c;
+    c.stride = col_stride(nR);
+    c.sw = reinterpret_cast<const T*>(base);
+    c.pw = c.sw + 2 * (size_t)c.stride;
+    c.so = reinterpret_cast<const int*>(c.pw + (size_t)dp * c.stride);
+    c.po = c.so + 2 * (size_t)c.stride;
+    return c;
+}
+// LDS of a strip: P1 and P2, four values per column and the zero entry.
+template <typename T>
+__host__ __device__ inline size_t strip_lds(int nR) {
+    return 2 * (size_t)(col_stride(nR) + 1) * kRows * sizeof(T);
+}
+
+// Column i's slots (DP predecessor slots).
+template <typename T, int DP>
+__device__ inline void build_col(const GraphRef& R, int i, Cols<T> c) {
+    const bool has = i < R.n;
+    const int sb = has ? R.rp[i] : 0, ns = has ? R.rp[i + 1] - sb : 0;
+    const int pb = has ? R.cp[i] : 0, np = has ? R.cp[i + 1] - pb : 0;
+    constexpr int vb = kRows * (int)sizeof(T);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const_cast<int*>(c.so)[q * c.stride + i] = (q < ns ? R.ci[sb + q] : c.stride) * vb;
+        const_cast<T*>(c.sw)[q * c.stride + i] = q < ns ? T(R.w[sb + q]) : T(0);
+    }
+#pragma unroll
+    for (int q = 0; q < DP; ++q) {
+        const_cast<int*>(c.po)[q * c.stride + i] = (q < np ? R.ri[pb + q] : c.stride) * vb;
+        const_cast<T*>(c.pw)[q * c.stride + i] = q < np ? T(R.w[R.eid[pb + q]]) : T(0);
+    }
+}
+
+// Merges the first `slots` list entries of rows c0 .. c0 + 3 (val(r, q) gives
+// entry q of row r: node and weight; len(r) its length) into sources: at each
+// step the smallest node at the head of any row, taken by every row that has
+// it there, so that every row's entries keep their order.
+template <typename T, int MAX, typename Len, typename Val>
+__device__ inline int merge_sources(int slots, Len len, Val val, int* src, T (*w)[kRows]) {
+    int head[kRows] = {0, 0, 0, 0};
+    int n = 0;
+    for (; n < MAX; ++n) {
+        int v = INT_MAX;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+            if (head[r] < min(len(r), slots)) {
+                T x;
+                v = min(v, val(r, head[r], x));
+            }
+        if (v == INT_MAX) break;
+        src[n] = v;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            T x = T(0);
+            bool take = false;
+            if (head[r] < min(len(r), slots)) take = val(r, head[r], x) == v;
+            w[n][r] = take ? x : T(0);
+            head[r] += take ? 1 : 0;
+        }
+    }
+    for (int q = n; q < MAX; ++q) {  // padding: a source that is read anyway, weight 0
+        src[q] = n > 0 ? src[0] : 0;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) w[q][r] = T(0);
+    }
+    return n;
+}
+
+// The table of the strip that starts at row c0 (one thread).
+template <typename T, int DP>
+__device__ inline void build_strip(const GraphRef& C, int c0, StripTab<T>* t) {
+    auto row = [&](int r) { return c0 + r < C.n ? c0 + r : -1; };
+    merge_sources<T, kSrcS>(
+        2, [&](int r) { return row(r) < 0 ? 0 : C.rp[row(r) + 1] - C.rp[row(r)]; },
+        [&](int r, int q, T& w) {
+            const int e = C.rp[row(r)] + q;
+            w = T(C.w[e]);
+            return C.ci[e];
+        },
+        t->src_s, t->ws);
+    t->np = merge_sources<T, kSrcP>(
+        DP, [&](int r) { return row(r) < 0 ? 0 : C.cp[row(r) + 1] - C.cp[row(r)]; },
+        [&](int r, int q, T& w) {
+            const int e = C.cp[row(r)] + q;
+            w = T(C.w[C.eid[e]]);
+            return C.ri[e];
+        },
+        t->src_p, t->wp);
+    int lng = 0;
+    for (int r = 0; r < kRows; ++r)
+        if (row(r) >= 0 &&
+            (C.rp[row(r) + 1] - C.rp[row(r)] > 2 || C.cp[row(r) + 1] - C.cp[row(r)] > DP))
+            lng |= 1 << r;
+    t->long_rows = lng;
+}
+
+template <typename T>
+struct Quad {
+    T v[kRows];
+};
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// acc[r] += w[r] * x for the strip's four rows (lane: one column of x).
+// FP32: one outer product per 64 columns, the weight of row (lane & 3) in wl.
+__device__ __forceinline__ void add_source(Quad<float>& acc, float wl, const float*, float x) {
+    floatx4 a = {acc.v[0], acc.v[1], acc.v[2], acc.v[3]};
+    a = __builtin_amdgcn_mfma_f32_4x4x1f32(wl, x, a, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc.v[r] = a[r];
+}
+__device__ __forceinline__ void add_source(Quad<double>& acc, double, const double* w, double x) {
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) acc.v[r] = dev::fma_t(w[r], x, acc.v[r]);
+}
+
+// Stage A: P1 and P2 of the strip (X: row stride nR) into LDS.  The whole
+// wave takes part in every source (the matrix instruction reads all lanes):
+// lanes past the last column read the last one.
+template <typename T>
+__device__ __forceinline__ void stage_sources(const T* X, int nR, const StripTab<T>* t, Quad<T>* P1, Quad<T>* P2) {
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int wave = dev::uni((int)threadIdx.x / kWave);
+    const int nch = (nR + kWave - 1) / kWave;
+    T ws[kSrcS], wp[kSrcFast];
+    int ss[kSrcS], sp[kSrcFast];
+#pragma unroll
+    for (int q = 0; q < kSrcS; ++q) {
+        ws[q] = t->ws[q][lane & (kRows - 1)];
+        ss[q] = dev::uni(t->src_s[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < kSrcFast; ++q) {
+        wp[q] = t->wp[q][lane & (kRows - 1)];
+        sp[q] = dev::uni(t->src_p[q]);
+    }
+    const int np = dev::uni(t->np);
+    if (threadIdx.x == 0) {
+        P1[col_stride(nR)] = Quad<T>{};
+        P2[col_stride(nR)] = Quad<T>{};
+    }
+    for (int ch = wave; ch < nch; ch += kWaves) {
+        const int col = ch * kWave + lane, at = min(col, nR - 1);
+        T xs[kSrcS], xp[kSrcFast];
+#pragma unroll
+        for (int q = 0; q < kSrcS; ++q) xs[q] = X[(long long)ss[q] * nR + at];
+#pragma unroll
+        for (int q = 0; q < kSrcFast; ++q) xp[q] = X[(long long)sp[q] * nR + at];
+        Quad<T> a{}, b{};
+#pragma unroll
+        for (int q = 0; q < kSrcS; ++q) add_source(a, ws[q], t->ws[q], xs[q]);
+#pragma unroll
+        for (int q = 0; q < kSrcFast; ++q) add_source(b, wp[q], t->wp[q], xp[q]);
+        for (int q = kSrcFast; q < np; ++q)
+            add_source(b, t->wp[q][lane & (kRows - 1)], t->wp[q], X[(long long)dev::uni(t->src_p[q]) * nR + at]);
+        P1[col] = a;
+        P2[col] = b;
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ const Quad<T>& quad_at(const Quad<T>* P, int off) {
+    return *reinterpret_cast<const Quad<T>*>(reinterpret_cast<const unsigned char*>(P) + off);
+}
+
+// Terms of a row c of C whose lists are longer than the slots (2 successors,
+// 4 predecessors), for column i, as the pair kernels add them: for a node i
+// within 2 successors and 3 predecessors the sum over i's slots inside the
+// sum over the rest of c's lists, else the other way round.
+template <typename T>
+__device__ __noinline__ T long_row_terms(const T* X, int nR, const GraphRef& R, const GraphRef& C, int i, int c) {
+    const int sb = R.rp[i], ns = R.rp[i + 1] - sb, pb = R.cp[i], np = R.cp[i + 1] - pb;
+    const int cs0 = C.rp[c] + 2, cs1 = C.rp[c + 1], cp0 = C.cp[c] + 4, cp1 = C.cp[c + 1];
+    T y = T(0);
+    if (ns <= 2 && np <= 3) {
+        for (int q = cs0; q < cs1; ++q) {
+            const T* row = X + (long long)C.ci[q] * nR;
+            T s = T(0);
+            for (int a = 0; a < ns; ++a) s = dev::fma_t(T(R.w[sb + a]), row[R.ci[sb + a]], s);
+            y = dev::fma_t(T(C.w[q]), s, y);
+        }
+        for (int q = cp0; q < cp1; ++q) {
+            const T* row = X + (long long)C.ri[q] * nR;
+            T s = T(0);
+            for (int b = 0; b < np; ++b) s = dev::fma_t(T(R.w[R.eid[pb + b]]), row[R.ri[pb + b]], s);
+            y = dev::fma_t(T(C.w[C.eid[q]]), s, y);
+        }
+    } else {
+        for (int a = 0; a < ns; ++a) {
+            T s = T(0);
+            for (int q = cs0; q < cs1; ++q)
+                s = dev::fma_t(T(C.w[q]), X[(long long)C.ci[q] * nR + R.ci[sb + a]], s);
+            y = dev::fma_t(T(R.w[sb + a]), s, y);
+        }
+        for (int b = 0; b < np; ++b) {
+            T s = T(0);
+            for (int q = cp0; q < cp1; ++q)
+                s = dev::fma_t(T(C.w[C.eid[q]]), X[(long long)C.ri[q] * nR + R.ri[pb + b]], s);
+            y = dev::fma_t(T(R.w[R.eid[pb + b]]), s, y);
+        }
+    }
+    return y;
+}
+
+// Stage B for one column (DP predecessor slots): the terms of its slots and,
+// when `rest` (some lane's lists are longer), those of longer lists, in list
+// order, successors before predecessors.
+template <typename T, int DP>
+__device__ __forceinline__ Quad<T> gather_col(const Cols<T>& c, int i, const Quad<T>* P1, const Quad<T>* P2,
+                                              bool rest, const GraphRef& R) {
+    Quad<T> y;
+    int so[2], po[DP];
+    T sw[2], pw[DP];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        so[q] = c.so[q * c.stride + i];
+        sw[q] = c.sw[q * c.stride + i];
+    }
+#pragma unroll
+    for (int q = 0; q < DP; ++q) {
+        po[q] = c.po[q * c.stride + i];
+        pw[q] = c.pw[q * c.stride + i];
+    }
+    {
+        const Quad<T> g = quad_at(P1, so[0]);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) y.v[r] = sw[0] * g.v[r];
+    }
+    {
+        const Quad<T> g = quad_at(P1, so[1]);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(sw[1], g.v[r], y.v[r]);
+    }
+    if (rest && i < R.n)
+        for (int e = R.rp[i] + 2; e < R.rp[i + 1]; ++e) {
+            const Quad<T> g = P1[R.ci[e]];
+            const T w = T(R.w[e]);
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(w, g.v[r], y.v[r]);
+        }
+#pragma unroll
+    for (int q = 0; q < DP; ++q) {
+        const Quad<T> g = quad_at(P2, po[q]);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(pw[q], g.v[r], y.v[r]);
+    }
+    if (rest && i < R.n)
+        for (int e = R.cp[i] + DP; e < R.cp[i + 1]; ++e) {
+            const Quad<T> g = P2[R.ri[e]];
+            const T w = T(R.w[R.eid[e]]);
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(w, g.v[r], y.v[r]);
+        }
+    return y;
+}
+
+}  // namespace strips
+}  // namespace cfsim
