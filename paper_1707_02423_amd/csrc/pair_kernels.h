@@ -1077,6 +1077,276 @@ __device__ __forceinline__ void greedy_walk_lds(const PairShape& sh, const T* S,
     }
 }
 
+// Candidates of the cached-best matchings: the value's bits plus one (0: none)
+// and the entry's (row, column) packed in the order of the original flat
+// index.  Bits order like values for numbers >= +0; a matrix with any other
+// entry (only from non-finite or negative weights) takes the sorted lists.
+template <typename T>
+struct Cand;
+template <>
+struct Cand<float> {
+    uint32_t v, k;
+    __device__ static uint32_t bits(float x) { return __float_as_uint(x); }
+    static constexpr uint32_t kMax = 0x7F7FFFFFu;
+};
+template <>
+struct Cand<double> {
+    uint64_t v;
+    uint32_t k;
+    __device__ static uint64_t bits(double x) { return (uint64_t)__double_as_longlong(x); }
+    static constexpr uint64_t kMax = 0x7FEFFFFFFFFFFFFFull;
+};
+template <typename T>
+__device__ __forceinline__ bool earlier(const Cand<T>& a, const Cand<T>& b) {
+    return a.v > b.v || (a.v == b.v && a.k < b.k);
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t max_step(uint32_t x) {
+    return max(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ uint64_t max_step(uint64_t x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), CTRL, 0xF, 0xF, true);
+    const uint64_t y = ((uint64_t)hi << 32) | lo;
+    return y > x ? y : x;
+}
+__device__ __forceinline__ uint32_t lane_bits(uint32_t x, int l) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+}
+__device__ __forceinline__ uint64_t lane_bits(uint64_t x, int l) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
+}
+// Earliest candidate of the first LANES lanes (16 or the whole wave), the same
+// in every lane: the largest value by lane moves, then its lane by a ballot;
+// the keys are only compared where several lanes hold that value.
+template <int LANES, typename T>
+__device__ __forceinline__ Cand<T> earliest(Cand<T> x) {
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    auto m = max_step<kDppXor1>(x.v);
+    m = max_step<kDppXor2>(m);
+    m = max_step<kDppHalfMirror>(m);
+    m = max_step<kDppMirror>(m);
+    auto t = lane_bits(m, 0);
+    if constexpr (LANES > 16) {
+#pragma unroll
+        for (int r = 16; r < kWave; r += 16) {
+            const auto o = lane_bits(m, r);
+            t = o > t ? o : t;
+        }
+    }
+    const uint64_t at = __ballot(x.v == t && (LANES > 16 || lane < 16));
+    Cand<T> g;
+    g.v = t;
+    g.k = (uint32_t)__builtin_amdgcn_readlane((int)x.k, (int)__builtin_ctzll(at));
+    if ((at & (at - 1)) != 0)
+        g.k = wave_min_u32(x.v == t && (LANES > 16 || lane < 16) ? x.k : 0xFFFFFFFFu);
+    return g;
+}
+
+// Step a7 by cached bests, S in LDS: lane l of wave w keeps, for each of its
+// columns l, l + 64, ..., the earliest free entry (greedy order) among the
+// wave's rows w, w + NW, ....  A pick is a wave maximum, one exchange of the
+// waves' candidates through LDS (one barrier) and the repair of what it took:
+// a column's lane forgets it, and the wave that owns the row rescans, for its
+// lanes whose best was on it, its few rows.  No lists are sorted, and every
+// wave works.  A pick is bound by the instructions on its path (a wave issues
+// one per 5 to 8 cycles), hence values as plain bits and keys compared only on
+// ties.  False (nothing written) if S has an entry that is not >= +0.
+template <typename T, int NT, int NCH>
+__device__ __forceinline__ bool greedy_bests(int nR, int nC, bool swp, const T* S, int* rstate, int* cstate,
+                                             double* red) {
+    constexpr int NW = NT / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = uni(tid / kWave);
+    const int rows = nR > wave ? (nR - wave + NW - 1) / NW : 0;
+    uint64_t alive = rows >= 64 ? ~0ull : (1ull << rows) - 1;
+    const int rsh = swp ? 0 : 16, csh = 16 - rsh;  // places of row and column in a key
+    bool bad = false;
+    // earliest entry of column c among the wave's free rows (a column's keys
+    // grow with the row: the first of equal values is the earliest)
+    auto scan = [&](int c, bool check) {
+        Cand<T> b{0, 0};
+        int br = 0;
+        for (int t0 = 0; t0 < rows; t0 += 4) {
+            T v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = S[min(wave + NW * (t0 + u), nR - 1) * nC + c];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const auto x = Cand<T>::bits(v[u]);
+                if (check) bad |= x > Cand<T>::kMax;
+                if (((alive >> ((t0 + u) & 63)) & 1) && x >= b.v) {
+                    b.v = x + 1;
+                    br = wave + NW * (t0 + u);
+                }
+            }
+        }
+        b.k = ((uint32_t)br << rsh) | ((uint32_t)c << csh);
+        return b;
+    };
+    Cand<T> best[NCH];
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+        const int c = ch * kWave + lane;
+        best[ch] = c < nC ? scan(c, true) : Cand<T>{0, 0};
+    }
+    if (__syncthreads_or(bad)) return false;
+    for (int r = tid; r < nR; r += NT) rstate[r] = -1;
+    for (int c = tid; c < nC; c += NT) cstate[c] = -1;
+    __syncthreads();  // cleared before the first pick is written
+    Cand<T>* slots = reinterpret_cast<Cand<T>*>(red);  // two areas of NW
+    const int need = min(nR, nC);
+    for (int done = 0; done < need; ++done) {
+        Cand<T> lb = best[0];
+#pragma unroll
+        for (int ch = 1; ch < NCH; ++ch)
+            if (earlier(best[ch], lb)) lb = best[ch];
+        lb = earliest<kWave>(lb);
+        Cand<T>* area = slots + (done & 1) * NW;
+        if (lane == 0) area[wave] = lb;
+        __syncthreads();
+        const Cand<T> g = earliest<16>(lane < NW ? area[lane] : Cand<T>{0, 0xFFFFFFFFu});
+        if (g.v == 0) break;  // the same in every thread
+        const int r0 = (int)((g.k >> rsh) & 0xFFFFu), c0 = (int)((g.k >> csh) & 0xFFFFu);
+        if (tid == 0) {
+            rstate[r0] = c0;
+            cstate[c0] = r0;
+        }
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch)
+            if (ch * kWave + lane == c0) best[ch].v = 0;
+        if ((r0 & (NW - 1)) == wave) {
+            alive &= ~(1ull << (r0 / NW));
+#pragma unroll
+            for (int ch = 0; ch < NCH; ++ch)
+                if (best[ch].v != 0 && (int)((best[ch].k >> rsh) & 0xFFFFu) == r0)
+                    best[ch] = scan(ch * kWave + lane, false);
+        }
+    }
+    __syncthreads();
+    return true;
+}
+
+// The same with S in global memory: wave w keeps the bests of the columns of
+// chunk w over all rows, two levels deep: per lane and segment of rows (in
+// LDS) and per lane.  A taken row costs its segment's rescan.
+template <typename T>
+__device__ __forceinline__ size_t best_segments_bytes(int nC, int segs) {
+    return (size_t)segs * ((nC + kWave - 1) / kWave * kWave) * sizeof(Cand<T>);
+}
+template <typename T, int NT>
+__device__ __forceinline__ bool greedy_segments(int nR, int nC, bool swp, const T* S, int* rstate, int* cstate,
+                                                void* room, size_t room_bytes, double* red) {
+    constexpr int NW = NT / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = uni(tid / kWave);
+    const int nCp = (nC + kWave - 1) / kWave * kWave;
+    int seg_rows = 16;
+    while (best_segments_bytes<T>(nC, (nR + seg_rows - 1) / seg_rows) > room_bytes) seg_rows += 4;
+    const int segs = (nR + seg_rows - 1) / seg_rows;
+    Cand<T>* seg_best = reinterpret_cast<Cand<T>*>(room);
+    const int rsh = swp ? 0 : 16, csh = 16 - rsh;  // places of row and column in a key
+    const int c = wave * kWave + lane;
+    const bool mine = c < nC;
+    const bool busy = wave * kWave < nC;
+    bool bad = false;
+    for (int r = tid; r < nR; r += NT) rstate[r] = -1;
+    for (int q = tid; q < nC; q += NT) cstate[q] = -1;
+    __syncthreads();
+    auto scan = [&](int s) {  // earliest entry of column c among segment s's free rows
+        Cand<T> b{0, 0};
+        int br = 0;
+        const int r1 = min((s + 1) * seg_rows, nR);
+        for (int r = s * seg_rows; r < r1; r += 8) {
+            T v[8];
+            int st[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                v[u] = S[(long long)min(r + u, nR - 1) * nC + (mine ? c : 0)];
+                st[u] = uni(rstate[min(r + u, nR - 1)]);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const auto x = Cand<T>::bits(v[u]);
+                bad |= x > Cand<T>::kMax;
+                if (r + u < r1 && st[u] == -1 && x >= b.v) {
+                    b.v = x + 1;
+                    br = r + u;
+                }
+            }
+        }
+        b.k = ((uint32_t)br << rsh) | ((uint32_t)c << csh);
+        return b;
+    };
+    Cand<T> best{0, 0};
+    if (busy) {
+        for (int s = 0; s < segs; ++s) {
+            const Cand<T> k = mine ? scan(s) : Cand<T>{0, 0};
+            seg_best[(size_t)s * nCp + c] = k;
+            if (earlier(k, best)) best = k;
+        }
+    }
+    if (__syncthreads_or(bad)) return false;
+    Cand<T>* slots = reinterpret_cast<Cand<T>*>(red);  // two areas of NW
+    const int need = min(nR, nC);
+    bool dead = !mine;
+    for (int done = 0; done < need; ++done) {
+        const Cand<T> lb = earliest<kWave>(best);
+        Cand<T>* area = slots + (done & 1) * NW;
+        if (lane == 0) area[wave] = lb;
+        __syncthreads();
+        const Cand<T> g = earliest<16>(lane < NW ? area[lane] : Cand<T>{0, 0xFFFFFFFFu});
+        if (g.v == 0) break;  // the same in every thread
+        const int r0 = (int)((g.k >> rsh) & 0xFFFFu), c0 = (int)((g.k >> csh) & 0xFFFFu);
+        // every wave marks the pick for itself before it scans (the same value)
+        rstate[r0] = c0;
+        if (tid == 0) cstate[c0] = r0;
+        if (c == c0) {
+            dead = true;
+            best.v = 0;
+        }
+        const int s0 = r0 / seg_rows;
+        if (busy) {
+            const Cand<T> sb = seg_best[(size_t)s0 * nCp + c];
+            const bool stale = !dead && sb.v != 0 && (int)((sb.k >> rsh) & 0xFFFFu) == r0;
+            if (__ballot(stale)) {
+                const Cand<T> k = scan(s0);  // the whole wave: it reads rows
+                if (stale) {
+                    seg_best[(size_t)s0 * nCp + c] = k;
+                    if ((int)((best.k >> rsh) & 0xFFFFu) == r0) {
+                        best = Cand<T>{0, 0};
+                        for (int s = 0; s < segs; ++s) {
+                            const Cand<T> q = seg_best[(size_t)s * nCp + c];
+                            if (earlier(q, best)) best = q;
+                        }
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    return true;
+}
+
+// Kept out of line: runs once per pair, and inlined it constrains the
+// register allocation of the update loop in the same kernel.  Its arguments
+// are scalars: a shape or list record passed by reference would have to live
+// in the caller's stack, written once per pair by every thread.
+template <typename T, int NT>
+__device__ __noinline__ bool greedy_in_lds(int nR, int nC, int swp, const T* S, int* rstate, int* cstate,
+                                           double* red) {
+    if (nC <= kWave) return greedy_bests<T, NT, 1>(nR, nC, swp != 0, S, rstate, cstate, red);
+    if (nC <= 2 * kWave) return greedy_bests<T, NT, 2>(nR, nC, swp != 0, S, rstate, cstate, red);
+    return greedy_bests<T, NT, 4>(nR, nC, swp != 0, S, rstate, cstate, red);
+}
+template <typename T, int NT>
+__device__ __noinline__ bool greedy_in_memory(int nR, int nC, int swp, const T* S, int* rstate, int* cstate,
+                                              void* room, size_t room_bytes, double* red) {
+    return greedy_segments<T, NT>(nR, nC, swp != 0, S, rstate, cstate, room, room_bytes, red);
+}
+
 // Kept out of line: runs once per pair, and inlined it constrains the
 // register allocation of the update loop in the same kernel.  Its arguments
 // are scalars: a shape or list record passed by reference would have to live
@@ -1267,7 +1537,7 @@ __device__ __forceinline__ void write_S(O* So, const T* S, long long total, int 
 // Step a7 and the outputs: greedy matching on the stored S (compute
 // orientation), its relative margin, score in original row order, S_out,
 // result.
-template <typename T, int NT>
+template <typename T, int NT, bool GLOBAL>
 __device__ __forceinline__ void match_and_write(const PairJob& J, int p, const GraphRef& A, const GraphRef& B, const PairShape& sh,
                                  const T* S, T* St, const Lists<T>& G, const IterOut& it, cfsim_pair_result* res,
                                  double* red, int* s_count) {
@@ -1277,7 +1547,20 @@ __device__ __forceinline__ void match_and_write(const PairJob& J, int p, const G
     const bool swp = sh.swap != 0;
     int* rstate = G.rstate;
     int* cstate = G.cstate;
-    if (nC <= kSortCols)
+    // One wave alone walks sorted lists; a workgroup keeps cached bests, unless
+    // a wave would have more rows (LDS) or there are more column chunks than
+    // waves (global memory) than its state holds: then sorted lists or rounds.
+    const size_t room = (size_t)(reinterpret_cast<unsigned char*>(G.rstate) - reinterpret_cast<unsigned char*>(G.rec));
+    bool matched = false;
+    if constexpr (!GLOBAL) {
+        if (NT > kWave && nC <= kSortCols && sh.nR <= 64 * NW)
+            matched = greedy_in_lds<T, NT>(sh.nR, nC, sh.swap, S, G.rstate, G.cstate, red);
+    } else {
+        if (nC <= NW * kWave && best_segments_bytes<T>(nC, 4) <= room)
+            matched = greedy_in_memory<T, NT>(sh.nR, nC, sh.swap, S, G.rstate, G.cstate, G.rec, room, red);
+    }
+    if (matched) {
+    } else if (nC <= kSortCols)
         greedy_sorted<T, NT>(sh.nR, nC, sh.swap, S, St, G.rstate, G.rbest, G.cstate, G.rec);
     else
         greedy_rounds<T, NT>(sh, S, St, G, s_count);
@@ -1381,7 +1664,7 @@ __device__ __forceinline__ void resized_pair(const PairJob& J, int p, const Grap
     GraphRef Am = A, Bm = B;  // outputs are n_M x n_M
     Am.n = M;
     Bm.n = M;
-    match_and_write<T, NT>(J, p, Am, Bm, shm, reinterpret_cast<const T*>(buf), reinterpret_cast<T*>(buf + SB), Gm,
+    match_and_write<T, NT, GLOBAL>(J, p, Am, Bm, shm, reinterpret_cast<const T*>(buf), reinterpret_cast<T*>(buf + SB), Gm,
                            it, res, red, s_count);
 }
 
@@ -1453,7 +1736,7 @@ __device__ __forceinline__ void lds_pair(const PairJob& J, int p, unsigned char*
     const Lists<T> G = carve_lists<T>(smem + 2 * sbytes, sh.nR, sh.nC, nnzR, nnzC);
     const T* S = reinterpret_cast<const T*>(smem + (it.final_buf ? sbytes : 0));
     T* St = reinterpret_cast<T*>(smem + (it.final_buf ? 0 : sbytes));
-    match_and_write<T, NT>(Jr, p, A, B, sh, S, St, G, it, res, red, s_count);
+    match_and_write<T, NT, false>(Jr, p, A, B, sh, S, St, G, it, res, red, s_count);
 }
 
 template <typename T, int NT, int NCH, int MODE>
@@ -1499,7 +1782,7 @@ __device__ __forceinline__ void global_pair(const PairJob& J, int p, unsigned ch
     } else {
         it = iterate_global<T, NT>(J, sh, G, S0, S1, degenerate, red, checkpoint_base<T>(J, p));
     }
-    match_and_write<T, NT>(J, p, A, B, sh, it.final_buf ? S1 : S0, it.final_buf ? S0 : S1, G, it, res, red, s_count);
+    match_and_write<T, NT, true>(J, p, A, B, sh, it.final_buf ? S1 : S0, it.final_buf ? S0 : S1, G, it, res, red, s_count);
 }
 
 // Persistent driver: one pair at a time per workgroup, pulled from the
@@ -1603,11 +1886,13 @@ void strip_finish_kernel(StripJob S) {
     __shared__ int s_count[2];
     const StripState st = *S.fin;
     const PairShape sh = make_shape(S.J.ga.n, S.J.gb.n, S.swap, kGlobalThreads / kWave);
-    const Lists<T> G = carve_lists<T>(smem, sh.nR, sh.nC, 0, 0);
+    // the matching's cached bests take the room of the lists: all of the LDS
+    const int spare = (int)((kGlobalLds - lds_lists_bytes(sh.nR, sh.nC, 0, 0, sizeof(T)) - 64) / (4 * sizeof(Edge<T>)));
+    const Lists<T> G = carve_lists<T>(smem, sh.nR, sh.nC, spare, spare);
     IterOut it{st.iters > 0 ? sqrt(st.tot) : 0.0, st.d2 >= 0.0 ? sqrt(st.d2) : __builtin_inf(), st.iters, st.status, 0};
     T* Sx = reinterpret_cast<T*>((st.iters & 1) ? S.x0 : S.x1);
     T* St = reinterpret_cast<T*>((st.iters & 1) ? S.x1 : S.x0);
-    match_and_write<T, kGlobalThreads>(S.J, 0, S.J.ga, S.J.gb, sh, Sx, St, G, it, S.J.res, red, s_count);
+    match_and_write<T, kGlobalThreads, true>(S.J, 0, S.J.ga, S.J.gb, sh, Sx, St, G, it, S.J.res, red, s_count);
 }
 
 // The kernel of one measure and arithmetic type for a bucket (instantiations
