@@ -830,6 +830,15 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
             job.gws = b.slots[v];
             job.slot_elems = resize ? cfsim::resized_slot_elems(set->max_nodes) : global_slot_elems(set->max_nodes);
             grid = ctx->grid[d][v];
+            if (resize || dm.on) {
+                grid = num_cus_of(ctx) * lds_blocks_per_cu(v, esize);
+            } else {
+                // one workgroup per CU; the slots of the others hold the strip tables
+                const long long slot = 2 * job.slot_elems * esize;
+                const int slots = num_cus_of(ctx) * lds_blocks_per_cu(v, esize);
+                job.tab_stride = slots > grid ? (slots - grid) * slot / grid / 256 * 256 : 0;
+                job.tabs = job.tab_stride > 0 ? static_cast<unsigned char*>(b.slots[v]) + grid * slot : nullptr;
+            }
         }
         if (timed && (e = (int)hipEventRecord(ctx->t0[v], st)) != 0) return e;
         if ((e = cfsim::launch_pair_lds(v, dtype, job, grid, st)) != 0) return e;

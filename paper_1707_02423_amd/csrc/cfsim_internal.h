@@ -178,7 +178,13 @@ __host__ __device__ inline size_t lds_pair_bytes(const PairShape& s, int nnzR, i
 // The global-memory kernel: one workgroup per pair, S_cur and S_next in a
 // workspace slot of `slot_elems` elements each; lists in LDS.
 constexpr int kGlobalThreads = 512;
-constexpr int kGlobalLds = 78 * 1024;
+constexpr int kGlobalLds = 78 * 1024;  // bound of a pair's lists
+// The plain measure's global kernel: in FP32 a whole CU per pair, on strips
+// (strips.h); in FP64 gathers from S, two workgroups per CU (on strips the
+// FP64 row sums have no matrix instruction: 34.4 against 25.0 ms for the
+// all-pairs batch of 96 graphs).
+__host__ __device__ constexpr int plain_global_threads(int esize) { return esize == 8 ? kGlobalThreads : 1024; }
+__host__ __device__ constexpr int plain_global_lds(int esize) { return esize == 8 ? kGlobalLds : 159 * 1024; }
 
 // Orientation that fills 64-lane chunks better (ties keep S as n_B x n_A).
 __host__ __device__ inline int preferred_swap(int nA, int nB) {
@@ -282,6 +288,10 @@ struct PairJob {
     // elements each); unused by the LDS kernels.
     void* gws;
     long long slot_elems;
+    // Plain global kernel: strip tables, `tab_stride` bytes per workgroup
+    // (NULL: none, the pairs run on gathers from S)
+    unsigned char* tabs;
+    long long tab_stride;
     // Forward checkpoints for the reverse mode (NULL: none): pair p's S_k for
     // k = c * ckpt_every (c = 1, 2, ...) at ckpt + ckpt_off[p] + (c - 1) n_A n_B,
     // n_B x n_A row-major, in the arithmetic type

@@ -134,8 +134,14 @@ const void* variant_kernel(int v, int dtype, int mode = kModePlain) {
     }
 }
 
-int threads_of(int v, int esize) { return v == kBucketGlobal ? kGlobalThreads : variant_info(v, esize).nt; }
-int lds_of(int v, int esize) { return v == kBucketGlobal ? kGlobalLds : variant_info(v, esize).lds_bytes; }
+int threads_of(int v, int esize, int mode) {
+    if (v == kBucketGlobal) return mode == kModePlain ? plain_global_threads(esize) : kGlobalThreads;
+    return variant_info(v, esize).nt;
+}
+int lds_of(int v, int esize, int mode) {
+    if (v == kBucketGlobal) return mode == kModePlain ? plain_global_lds(esize) : kGlobalLds;
+    return variant_info(v, esize).lds_bytes;
+}
 
 }  // namespace
 
@@ -148,8 +154,8 @@ int launch_pair_lds(int variant, int dtype, const PairJob& job, int grid, hipStr
     void* args[] = {const_cast<PairJob*>(&job)};
     const int mode = job.damped ? kModeDamped : (job.resize ? kModeResized : kModePlain);
     return (int)hipLaunchKernel(variant_kernel(variant, dtype, mode), dim3(grid),
-                                dim3(threads_of(variant, esize)), args,
-                                (size_t)lds_of(variant, esize), stream);
+                                dim3(threads_of(variant, esize, mode)), args,
+                                (size_t)lds_of(variant, esize, mode), stream);
 }
 
 int launch_plan(const PlanJob& job, hipStream_t stream) {
@@ -181,9 +187,9 @@ int set_kernel_attributes() {
     for (int v = 0; v <= kBucketGlobal; ++v)
         for (int mode = kModePlain; mode <= kModeResized; ++mode) {
             e |= (int)hipFuncSetAttribute(variant_kernel(v, CFSIM_F32, mode),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds_of(v, 4));
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds_of(v, 4, mode));
             e |= (int)hipFuncSetAttribute(variant_kernel(v, CFSIM_F64, mode),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds_of(v, 8));
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds_of(v, 8, mode));
         }
     return e;
 }
@@ -191,7 +197,8 @@ int set_kernel_attributes() {
 int occupancy_of(int variant, int dtype, int* blocks) {
     const int esize = dtype == CFSIM_F64 ? 8 : 4;
     return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, variant_kernel(variant, dtype),
-                                                            threads_of(variant, esize), (size_t)lds_of(variant, esize));
+                                                            threads_of(variant, esize, kModePlain),
+                                                            (size_t)lds_of(variant, esize, kModePlain));
 }
 
 }  // namespace cfsim

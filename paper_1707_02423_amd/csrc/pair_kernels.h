@@ -30,6 +30,7 @@
 #include "cfsim_internal.h"
 #include "pair_device.h"
 #include "strip_job.h"
+#include "strips.h"
 
 namespace cfsim {
 
@@ -422,6 +423,149 @@ __device__ __forceinline__ IterOut iterate_global(const PairJob& J, const PairSh
         __syncthreads();
     }
     out.final_buf = cur;
+    return out;
+}
+
+// Steps a4-a6 with the iterates in global memory, on strips of four rows of
+// X = S^T (strips.h), one strip per wave and step, the wave's P1 and P2 in
+// LDS.  X_0 (nC x nR, all entries s0) stands in B0; `tabs` is the workgroup's
+// table area; the column lists and P1, P2 take `lds` (room for `waves` waves).
+// Reads of X are consecutive where the gathers from S took a cache line per
+// few lanes, and only they leave the CU.  Leaves S (nR x nC) in the buffer
+// `final_buf` names.
+constexpr int kStripDP = 4;  // predecessor slots (kDP) of the column lists
+
+template <typename T>
+__device__ inline int strip_waves(int nR, int nw, size_t lds_bytes) {
+    const size_t cols = align16(strips::cols_bytes<T>(nR, kStripDP));
+    if (cols >= lds_bytes) return 0;
+    const size_t w = (lds_bytes - cols) / strips::strip_lds<T>(nR);
+    return w < (size_t)nw ? (int)w : nw;
+}
+
+template <typename T, int NT>
+__device__ __forceinline__ IterOut iterate_strips(const PairJob& J, const PairShape& sh, const GraphRef& R,
+                                                  const GraphRef& C, T* B0, T* B1, unsigned char* tab_area,
+                                                  unsigned char* lds, int waves, bool degenerate, double* red, T* ck) {
+    using namespace strips;
+    constexpr int NW = NT / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = uni(tid / kWave);
+    const int nR = sh.nR, nC = sh.nC, nch = (nR + kWave - 1) / kWave;
+    IterOut out{0.0, __builtin_inf(), 0, 0u, 0};
+    if (degenerate) {
+        out.status = CFSIM_DEGENERATE;
+        return out;
+    }
+    const int n_strips = (nC + kRows - 1) / kRows;
+    StripTab<T>* tabs = reinterpret_cast<StripTab<T>*>(tab_area);
+    for (int s = tid; s < n_strips; s += NT) build_strip<T, kStripDP>(C, s * kRows, nR, tabs + s);
+    const Cols<T> cols = carve_cols<T>(lds, nR, kStripDP);
+    for (int i = tid; i < cols.stride; i += NT) build_col<T, kStripDP>(R, i, cols);
+    Quad<T>* P1 = reinterpret_cast<Quad<T>*>(lds + align16(cols_bytes<T>(nR, kStripDP)) +
+                                             (wave < waves ? wave : 0) * strip_lds<T>(nR));
+    Quad<T>* P2 = P1 + col_stride(nR) + 1;
+    if (wave < waves && lane < 2) (lane ? P2 : P1)[col_stride(nR)] = Quad<T>{};
+    bool lng = false;  // some column's lists are longer than the slots
+    for (int i = tid; i < nR; i += NT) lng |= R.rp[i + 1] - R.rp[i] > 2 || R.cp[i + 1] - R.cp[i] > kStripDP;
+    const bool any_long = __syncthreads_or(lng) != 0;
+    T* Xc = B0;
+    T* Xn = B1;
+    int cur = 0;
+    T sigma = T(1);
+    double a_even = 1.0;  // 1/nu of the last even iterate (S_0 is stored normalised)
+    for (int k = 1; k <= J.max_iter; ++k) {
+        const bool even = (k & 1) == 0;
+        EvenSums es{0.0, 0.0, 0.0};
+        if (wave < waves)
+            for (int s = wave; s < n_strips; s += waves) {
+                const int c0 = s * kRows;
+                const StripTab<T>* tab = tabs + s;
+                wave_sources(Xc, nR, tab, P1, P2);
+                const int long_rows = uni(tab->long_rows);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const uint32_t rowb = (uint32_t)nR * (uint32_t)sizeof(T);
+                const int left = nC - c0;
+                for (int ch = 0; ch < nch; ++ch) {
+                    const int i = ch * kWave + lane;
+                    const bool valid = i < nR;
+                    const uint32_t o = (uint32_t)c0 * rowb + (uint32_t)min(i, nR - 1) * (uint32_t)sizeof(T);
+                    T old[kRows] = {};
+                    if (even) {
+#pragma unroll
+                        for (int r = 0; r < kRows; ++r) old[r] = at_byte(Xn, o + (r < left ? r : 0) * rowb);
+                    }
+                    Quad<T> y = gather_col<T, kStripDP>(cols, i, P1, P2, any_long, R);
+                    if (long_rows)
+                        for (int r = 0; r < kRows; ++r)
+                            if (((long_rows >> r) & 1) && valid) {
+                                const T add = long_row_terms<T>(Xc, nR, R, C, i, c0 + r);
+#pragma unroll
+                                for (int z = 0; z < kRows; ++z) y.v[z] += z == r ? add : T(0);
+                            }
+                    if (valid) {
+#pragma unroll
+                        for (int r = 0; r < kRows; ++r) {
+                            if (r >= left) break;
+                            const T f = y.v[r] * sigma;
+                            *reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(Xn) + (o + r * rowb)) = f;
+                            es.nu2 += (double)f * (double)f;
+                            if (even) even_terms(es, f, old[r]);
+                        }
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+        if (even)
+            es = block_sum_even<NW>(es, red);
+        const double tot = even ? es.nu2 : block_sum<NW>(es.nu2, red + 3 * NW);
+        if (!(tot > 0.0) || !isfinite(tot)) {  // cannot normalise: keep S_{k-1}
+            out.status = CFSIM_DEGENERATE;
+            break;
+        }
+        out.nu = sqrt(tot);
+        out.iters = k;
+        const double inv = 1.0 / out.nu;
+        sigma = T(inv);
+        T* t = Xc;
+        Xc = Xn;
+        Xn = t;
+        cur ^= 1;
+        if (ck && k % J.ckpt_every == 0) {
+            // S_k = sigma X_k^T in the n_B x n_A orientation
+            T* dst = ck + (long long)(k / J.ckpt_every - 1) * nR * nC;
+            if (sh.swap) {
+                for (int o = tid; o < nR * nC; o += NT) dst[o] = Xc[o] * sigma;
+            } else {
+                for (int i = wave; i < nR; i += NW)
+                    for (int c = lane; c < nC; c += kWave) dst[(long long)i * nC + c] = Xc[(long long)c * nR + i] * sigma;
+            }
+        }
+        if (even) {
+            out.delta = even_step_delta(es, a_even, inv);
+            a_even = inv;
+            if (out.delta < J.tol) {
+                out.status = CFSIM_CONVERGED;
+                break;
+            }
+        }
+    }
+    if (out.status == 0) out.status = CFSIM_HIT_MAX_ITER;
+    // S = sigma X^T into the other buffer, in 32 x 32 tiles through LDS
+    __syncthreads();
+    T(*tile)[33] = reinterpret_cast<T(*)[33]>(lds);
+    const int tx = tid & 31, ty = tid >> 5;
+    const int ntc = (nC + 31) / 32, ntiles = ntc * ((nR + 31) / 32);
+    for (int t = 0; t < ntiles; ++t) {
+        const int i0 = (t / ntc) * 32, j0 = (t % ntc) * 32;
+        for (int y = ty; y < 32; y += NT / 32)
+            if (j0 + y < nC && i0 + tx < nR) tile[y][tx] = Xc[(long long)(j0 + y) * nR + i0 + tx] * sigma;
+        __syncthreads();
+        for (int y = ty; y < 32; y += NT / 32)
+            if (i0 + y < nR && j0 + tx < nC) Xn[(long long)(i0 + y) * nC + j0 + tx] = tile[tx][y];
+        __syncthreads();
+    }
+    out.final_buf = cur ^ 1;
     return out;
 }
 
@@ -1769,8 +1913,26 @@ __device__ __forceinline__ void global_pair(const PairJob& J, int p, unsigned ch
     T* S0 = slot;
     T* S1 = slot + J.slot_elems;
     const T s0 = T(1.0 / sqrt((double)nR * (double)nC));
-    const bool degenerate = stage_pair<T, NT>(R, C, nR, nC, G, S0, s0);
     IterOut it;
+    if constexpr (MODE == kModePlain && sizeof(T) == 4) {
+        // on strips where their tables and two waves' rows fit (the old
+        // workspace of a plain pair holds no tables)
+        const int waves = strip_waves<T>(nR, NT / kWave, (size_t)plain_global_lds((int)sizeof(T)));
+        if (J.tabs && waves >= 2 &&
+            (long long)((nC + strips::kRows - 1) / strips::kRows) * (long long)sizeof(strips::StripTab<T>) <= J.tab_stride) {
+            int pos_r = 0, pos_c = 0;
+            for (int t = threadIdx.x; t < R.nnz; t += NT) pos_r |= R.w[t] > 0.0;
+            for (int t = threadIdx.x; t < C.nnz; t += NT) pos_c |= C.w[t] > 0.0;
+            for (long long t = threadIdx.x; t < (long long)nR * nC; t += NT) S0[t] = s0;
+            const int any_r = __syncthreads_or(pos_r), any_c = __syncthreads_or(pos_c);
+            it = iterate_strips<T, NT>(J, sh, R, C, S0, S1, J.tabs + (size_t)blockIdx.x * J.tab_stride, smem, waves,
+                                       !(any_r && any_c), red, checkpoint_base<T>(J, p));
+            match_and_write<T, NT, true>(J, p, A, B, sh, it.final_buf ? S1 : S0, it.final_buf ? S0 : S1, G, it, res, red,
+                                         s_count);
+            return;
+        }
+    }
+    const bool degenerate = stage_pair<T, NT>(R, C, nR, nC, G, S0, s0);
     if constexpr (DAMPED) {
         DampedPrior P;
         if (!damped_prior<T, NT>(J, p, A.n, B.n, sh, P, red)) {
@@ -1850,12 +2012,13 @@ void resized_lds_kernel(PairJob J) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(kGlobalThreads) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ __launch_bounds__(plain_global_threads((int)sizeof(T))) __attribute__((amdgpu_waves_per_eu(4)))
 void pair_global_kernel(PairJob J) {
+    constexpr int NT = plain_global_threads((int)sizeof(T));
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[4 * (kGlobalThreads / kWave)];
+    __shared__ double red[4 * (NT / kWave)];
     __shared__ int s_item, s_count[2];
-    drive<true, T, kGlobalThreads, 1, kModePlain>(J, smem, red, &s_item, s_count, nullptr);
+    drive<true, T, NT, 1, kModePlain>(J, smem, red, &s_item, s_count, nullptr);
 }
 
 template <typename T>

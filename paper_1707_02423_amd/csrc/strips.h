@@ -29,15 +29,16 @@ constexpr int kSrcS = 8;           // merged successor sources of a strip (4 row
 constexpr int kSrcP = 16;          // merged predecessor sources (4 rows, at most 4 each)
 constexpr int kSrcFast = 8;        // predecessor sources whose reads are issued together
 
-// Sources of one strip: rows of X and the four rows' weights of each.
+// Sources of one strip: byte offsets of rows of X and the four rows' weights
+// of each.
 template <typename T>
 struct alignas(16) StripTab {
     T ws[kSrcS][kRows];
     T wp[kSrcP][kRows];
     int src_s[kSrcS], src_p[kSrcP];
-    int np;                        // predecessor sources past the fast ones are looped over
+    int ns, np;                    // sources
     int long_rows;                 // bit r: row r has list entries past the slots
-    int pad[2];
+    int pad;
 };
 
 // Lists of the columns (R nodes), one array per slot of `stride` entries:
@@ -127,11 +128,12 @@ __device__ inline int merge_sources(int slots, Len len, Val val, int* src, T (*w
     return n;
 }
 
-// The table of the strip that starts at row c0 (one thread).
+// The table of the strip that starts at row c0 (one thread; X's row stride
+// is nR, its bytes fit 31 bits).
 template <typename T, int DP>
-__device__ inline void build_strip(const GraphRef& C, int c0, StripTab<T>* t) {
+__device__ inline void build_strip(const GraphRef& C, int c0, int nR, StripTab<T>* t) {
     auto row = [&](int r) { return c0 + r < C.n ? c0 + r : -1; };
-    merge_sources<T, kSrcS>(
+    t->ns = merge_sources<T, kSrcS>(
         2, [&](int r) { return row(r) < 0 ? 0 : C.rp[row(r) + 1] - C.rp[row(r)]; },
         [&](int r, int q, T& w) {
             const int e = C.rp[row(r)] + q;
@@ -153,6 +155,14 @@ __device__ inline void build_strip(const GraphRef& C, int c0, StripTab<T>* t) {
             (C.rp[row(r) + 1] - C.rp[row(r)] > 2 || C.cp[row(r) + 1] - C.cp[row(r)] > DP))
             lng |= 1 << r;
     t->long_rows = lng;
+    for (int q = 0; q < kSrcS; ++q) t->src_s[q] *= nR * (int)sizeof(T);
+    for (int q = 0; q < kSrcP; ++q) t->src_p[q] *= nR * (int)sizeof(T);
+}
+
+// Entry at a byte offset of an iterate.
+template <typename T>
+__device__ __forceinline__ T at_byte(const T* X, uint32_t off) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(X) + off);
 }
 
 template <typename T>
@@ -203,16 +213,108 @@ __device__ __forceinline__ void stage_sources(const T* X, int nR, const StripTab
         const int col = ch * kWave + lane, at = min(col, nR - 1);
         T xs[kSrcS], xp[kSrcFast];
 #pragma unroll
-        for (int q = 0; q < kSrcS; ++q) xs[q] = X[(long long)ss[q] * nR + at];
+        for (int q = 0; q < kSrcS; ++q) xs[q] = at_byte(X, (uint32_t)ss[q] + (uint32_t)at * (uint32_t)sizeof(T));
 #pragma unroll
-        for (int q = 0; q < kSrcFast; ++q) xp[q] = X[(long long)sp[q] * nR + at];
+        for (int q = 0; q < kSrcFast; ++q) xp[q] = at_byte(X, (uint32_t)sp[q] + (uint32_t)at * (uint32_t)sizeof(T));
         Quad<T> a{}, b{};
 #pragma unroll
         for (int q = 0; q < kSrcS; ++q) add_source(a, ws[q], t->ws[q], xs[q]);
 #pragma unroll
         for (int q = 0; q < kSrcFast; ++q) add_source(b, wp[q], t->wp[q], xp[q]);
         for (int q = kSrcFast; q < np; ++q)
-            add_source(b, t->wp[q][lane & (kRows - 1)], t->wp[q], X[(long long)dev::uni(t->src_p[q]) * nR + at]);
+            add_source(b, t->wp[q][lane & (kRows - 1)], t->wp[q],
+                       at_byte(X, (uint32_t)dev::uni(t->src_p[q]) + (uint32_t)at * (uint32_t)sizeof(T)));
+        P1[col] = a;
+        P2[col] = b;
+    }
+}
+
+// Stage A by one wave, all chunks, into its own P1 and P2 (strips of
+// workgroups that stay with their pair).  FP32: one register holds the weights
+// of 16 sources (lane 4 q + r), of which the matrix instruction broadcasts the
+// block it needs (cbsz = 4, abid = the source).
+template <int Q>
+__device__ __forceinline__ void add_block(floatx4& acc, float w, float x) {
+    acc = __builtin_amdgcn_mfma_f32_4x4x1f32(w, x, acc, 4, Q, 0);
+}
+template <int W>
+__device__ __forceinline__ void add_blocks(floatx4& acc, float w, const float (&x)[4]) {
+    add_block<W>(acc, w, x[0]);
+    add_block<W + 1>(acc, w, x[1]);
+    add_block<W + 2>(acc, w, x[2]);
+    add_block<W + 3>(acc, w, x[3]);
+}
+__device__ __forceinline__ void wave_sources(const float* X, int nR, const StripTab<float>* t, Quad<float>* P1,
+                                             Quad<float>* P2) {
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const float* wt = &t->ws[0][0];  // ws and wp lie one behind the other
+    const float w = wt[lane], w2 = wt[64 + (lane & 31)];
+    const int src = t->src_s[lane < 24 ? lane : 0];  // src_s and src_p too
+    const int ns = dev::uni(t->ns), np = dev::uni(t->np);
+    const int nch = (nR + kWave - 1) / kWave;
+    for (int ch = 0; ch < nch; ++ch) {
+        const int col = ch * kWave + lane;
+        const uint32_t at = (uint32_t)min(col, nR - 1) * 4u;
+        float x[6][4];
+        auto read = [&](int g, int q0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[g][q] = at_byte(X, (uint32_t)dev::lane_value(src, q0 + q) + at);
+        };
+        read(0, 0);
+        read(2, 8);
+        if (ns > 4) read(1, 4);
+        if (np > 4) read(3, 12);
+        floatx4 a = {0.0f, 0.0f, 0.0f, 0.0f}, b = {0.0f, 0.0f, 0.0f, 0.0f};
+        add_blocks<0>(a, w, x[0]);
+        add_blocks<8>(b, w, x[2]);
+        if (ns > 4) add_blocks<4>(a, w, x[1]);
+        if (np > 4) add_blocks<12>(b, w, x[3]);
+        if (np > 8) {
+            read(4, 16);
+            add_blocks<0>(b, w2, x[4]);
+        }
+        if (np > 12) {
+            read(5, 20);
+            add_blocks<4>(b, w2, x[5]);
+        }
+        *reinterpret_cast<floatx4*>(&P1[col]) = a;
+        *reinterpret_cast<floatx4*>(&P2[col]) = b;
+    }
+}
+__device__ __forceinline__ void wave_sources(const double* X, int nR, const StripTab<double>* t, Quad<double>* P1,
+                                             Quad<double>* P2) {
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int src = t->src_s[lane < 24 ? lane : 0];  // src_s and src_p lie one behind the other
+    const int ns = dev::uni(t->ns), np = dev::uni(t->np);
+    const int nch = (nR + kWave - 1) / kWave;
+    for (int ch = 0; ch < nch; ++ch) {
+        const int col = ch * kWave + lane;
+        const uint32_t at = (uint32_t)min(col, nR - 1) * 8u;
+        double x[4][4];
+        auto read = [&](int g, int q0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[g][q] = at_byte(X, (uint32_t)dev::lane_value(src, q0 + q) + at);
+        };
+        Quad<double> a{}, b{};
+        auto add = [&](Quad<double>& acc, int g, const double (*w)[kRows]) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) acc.v[r] = dev::fma_t(w[q][r], x[g][q], acc.v[r]);
+        };
+        read(0, 0);
+        read(2, 8);
+        if (ns > 4) read(1, 4);
+        if (np > 4) read(3, 12);
+        add(a, 0, t->ws);
+        add(b, 2, t->wp);
+        if (ns > 4) add(a, 1, t->ws + 4);
+        if (np > 4) add(b, 3, t->wp + 4);
+        for (int q = 8; q < np; q += 4) {
+#pragma unroll
+            for (int z = 0; z < 4; ++z) x[0][z] = at_byte(X, (uint32_t)dev::uni(t->src_p[q + z]) + at);
+            add(b, 0, t->wp + q);
+        }
         P1[col] = a;
         P2[col] = b;
     }

@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256) void strip_build(StripJob S) {
     const Cols<T> cols = carve_cols<T>(S.cols, S.nR, kDP);
     for (int i = tid; i < cols.stride; i += nt) build_col<T, kDP>(R, i, cols);
     StripTab<T>* tabs = reinterpret_cast<StripTab<T>*>(S.tabs);
-    for (int s = tid; s < S.strips; s += nt) build_strip<T, kDP>(C, s * kRows, tabs + s);
+    for (int s = tid; s < S.strips; s += nt) build_strip<T, kDP>(C, s * kRows, S.nR, tabs + s);
     const T s0 = T(1.0 / sqrt((double)S.nR * (double)S.nC));
     T* X = reinterpret_cast<T*>(S.x0);
     for (long long t = tid; t < (long long)S.nR * S.nC; t += nt) X[t] = s0;
