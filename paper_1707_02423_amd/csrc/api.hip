@@ -25,6 +25,8 @@ struct cfsim_context {
     int num_cus = 0;
     int grid[2][cfsim::kBucketGlobal + 1] = {};  // persistent grid per [dtype][LDS variant | global]
     hipStream_t cap = nullptr;              // capture stream of the cached graphs
+    hipStream_t side = nullptr;             // its branch for the global-memory bucket
+    hipEvent_t fork = nullptr, join = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<unsigned char> key;         // arguments the cached graph was built for
@@ -453,9 +455,12 @@ cfsim_status cfsim_context_create(cfsim_context** out, int device) {
         delete ctx;
         return hip_fail(e, "hipGetSymbolAddress(scratch)");
     }
-    if ((e = (int)hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking)) != 0) {
-        delete ctx;
-        return hip_fail(e, "hipStreamCreateWithFlags");
+    if ((e = (int)hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking)) != 0 ||
+        (e = (int)hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking)) != 0 ||
+        (e = (int)hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming)) != 0 ||
+        (e = (int)hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming)) != 0) {
+        cfsim_context_destroy(ctx);
+        return hip_fail(e, "capture streams");
     }
     *out = ctx;
     return ok();
@@ -468,6 +473,9 @@ void cfsim_context_destroy(cfsim_context* ctx) {
     if (ctx->large_exec) (void)hipGraphExecDestroy(ctx->large_exec);
     if (ctx->large_graph) (void)hipGraphDestroy(ctx->large_graph);
     if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
+    if (ctx->side) (void)hipStreamDestroy(ctx->side);
+    if (ctx->fork) (void)hipEventDestroy(ctx->fork);
+    if (ctx->join) (void)hipEventDestroy(ctx->join);
     for (int v = 0; v < cfsim::kBuckets; ++v) {
         if (ctx->t0[v]) (void)hipEventDestroy(ctx->t0[v]);
         if (ctx->t1[v]) (void)hipEventDestroy(ctx->t1[v]);
@@ -813,10 +821,19 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
     job.prior = dm.prior;
     job.prior_off = dm.prior_off;
     const int d = dtype_index(dtype);
-    // The bucket kernels run one after another on the caller's stream, each
-    // with the whole device: a bucket's persistent grid drains its queue
-    // longest pair first, so its tail is about one pair long.
-    for (int v = 0; v < cfsim::kBuckets; ++v) {
+    // The LDS bucket kernels run one after another, each with the whole
+    // device: a bucket's persistent grid drains its queue longest pair first,
+    // so its tail is about one pair long.  The global-memory bucket holds the
+    // largest pairs, often fewer than CUs; in a captured call it runs beside
+    // the others on a branch of the graph, started first.
+    const bool branch = st == ctx->cap && !timed;
+    if (branch) {
+        if ((e = (int)hipEventRecord(ctx->fork, st)) != 0) return e;
+        if ((e = (int)hipStreamWaitEvent(ctx->side, ctx->fork, 0)) != 0) return e;
+    }
+    const int bucket_order[cfsim::kBuckets] = {cfsim::kBucketGlobal, 0, 1, 2, 3, 4, cfsim::kBucketInvalid};
+    static_assert(cfsim::kBucketGlobal == 5 && cfsim::kBuckets == 7, "bucket_order names every bucket");
+    for (const int v : bucket_order) {
         if (filter && v == cfsim::kBucketInvalid) continue;  // the FP64 pass leaves no pair invalid
         job.bounds = b.bounds + 2 * v;
         job.queue = b.queues + v;
@@ -841,8 +858,13 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
             }
         }
         if (timed && (e = (int)hipEventRecord(ctx->t0[v], st)) != 0) return e;
-        if ((e = cfsim::launch_pair_lds(v, dtype, job, grid, st)) != 0) return e;
+        hipStream_t vs = branch && v == cfsim::kBucketGlobal ? ctx->side : st;
+        if ((e = cfsim::launch_pair_lds(v, dtype, job, grid, vs)) != 0) return e;
         if (timed && (e = (int)hipEventRecord(ctx->t1[v], st)) != 0) return e;
+    }
+    if (branch) {
+        if ((e = (int)hipEventRecord(ctx->join, ctx->side)) != 0) return e;
+        if ((e = (int)hipStreamWaitEvent(st, ctx->join, 0)) != 0) return e;
     }
     (void)esize;
     return 0;
