@@ -268,14 +268,16 @@ void append_key(std::vector<unsigned char>& k, const X& x) {
 //   | part_nu, part_delta, tile_pair [n_pairs * large_tiles(max_nodes)]
 //   | node records [n_pairs][2][max_nodes]
 //   | nslots iterate slots of max_nodes^2 per pair (4, or 6 when resized)
+//   | without resize: strip lists and tables per pair
 int large_nslots(const cfsim_options* o) { return o->resize == CFSIM_RESIZE_BILINEAR ? 6 : 4; }
 
 size_t large_ws_bytes(int64_t n_pairs, int max_nodes, int esize, int nslots) {
-    const size_t tiles = (size_t)n_pairs * (size_t)cfsim::large_tiles(max_nodes);
+    const size_t parts = (size_t)n_pairs * (size_t)cfsim::large_parts(max_nodes);
     return align256((size_t)n_pairs * sizeof(cfsim::LargeState)) + align256((size_t)(n_pairs + 1) * 8) +
-           2 * align256(tiles * 8) + align256(tiles * 4) +
+           2 * align256(parts * 8) + align256(parts * 4) +
            align256((size_t)n_pairs * 2 * max_nodes * cfsim::large_rec_bytes(esize)) +
-           align256((size_t)n_pairs * nslots * (size_t)global_slot_elems(max_nodes) * (size_t)esize);
+           align256((size_t)n_pairs * nslots * (size_t)global_slot_elems(max_nodes) * (size_t)esize) +
+           (nslots == 4 ? (size_t)n_pairs * align256(cfsim::large_strip_bytes(max_nodes, esize)) : 0);
 }
 
 // MFMA variant, after the tiled-path workspace: block lists [n_pairs][2][idx
@@ -304,7 +306,7 @@ cfsim::LargeJob large_job(const cfsim_options* opt, int64_t n_pairs, int max_nod
     J.S_out = S_out;
     J.S_off = S_off;
     unsigned char* p = static_cast<unsigned char*>(ws);
-    const size_t tiles = (size_t)n_pairs * (size_t)cfsim::large_tiles(max_nodes);
+    const size_t tiles = (size_t)n_pairs * (size_t)cfsim::large_parts(max_nodes);
     J.st = reinterpret_cast<cfsim::LargeState*>(p);
     p += align256((size_t)n_pairs * sizeof(cfsim::LargeState));
     J.tile_off = reinterpret_cast<long long*>(p);
@@ -321,6 +323,12 @@ cfsim::LargeJob large_job(const cfsim_options* opt, int64_t n_pairs, int max_nod
     J.nslots = large_nslots(opt);
     J.slot_elems = global_slot_elems(max_nodes);
     p += align256((size_t)n_pairs * J.nslots * (size_t)J.slot_elems * (size_t)esize_of(opt->dtype));
+    if (J.nslots == 4) {
+        J.strips = !mfma_bf16(opt) && cfsim::large_on_strips(max_nodes, esize_of(opt->dtype));
+        J.strip_area = p;
+        J.strip_stride = (long long)align256(cfsim::large_strip_bytes(max_nodes, esize_of(opt->dtype)));
+        p += (size_t)n_pairs * (size_t)J.strip_stride;
+    }
     if (mfma_bf16(opt)) {
         const size_t nb = (size_t)(max_nodes + 31) / 32;
         J.mfma = 1;

@@ -425,6 +425,11 @@ struct LargeJob {
     void* bufs;          // [n_pairs][nslots][slot_elems]: 4 rotating iterates (+ V, S when resized)
     int nslots;
     long long slot_elems;
+    // strips: plain pairs run on strips of four rows of S^T (large_strip):
+    // column lists and strip tables of each pair, strip_stride bytes apart
+    int strips;
+    unsigned char* strip_area;
+    long long strip_stride;
     void* recs;          // [n_pairs][2][max_nodes] node records: rows of the row graph, columns of the column graph
     // BF16 MFMA tile products (CFSIM_FLAG_MFMA_BF16; plain FP32 pairs only)
     int mfma;
@@ -452,6 +457,13 @@ int launch_mfma_update(const LargeJob& job, int k, int grid, hipStream_t stream)
 // Bytes of one node record of the tiled path (first 2 successors, 3 predecessors).
 __host__ __device__ inline size_t large_rec_bytes(int esize) { return esize == 8 ? 80 : 48; }
 __host__ __device__ inline long long large_tiles(int n) { return (long long)((n + 127) / 128) * ((n + 63) / 64); }
+// Norm partials per pair: its tiles, or its strips of four rows.
+__host__ __device__ inline long long large_parts(int n) {
+    const long long t = large_tiles(n), s = (n + 3) / 4;
+    return t > s ? t : s;
+}
+size_t large_strip_bytes(int max_nodes, int esize);  // column lists and strip tables of one pair
+bool large_on_strips(int max_nodes, int esize);      // whether a strip's rows fit LDS
 int large_step_grid(int num_cus);
 int set_large_attributes();
 int launch_large(int dtype, const LargeJob& job, int grid, hipStream_t stream);

@@ -31,6 +31,7 @@
 #include "cfsim_internal.h"
 #include "large_tiles.h"
 #include "pair_device.h"
+#include "strips.h"
 
 namespace cfsim {
 
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(256) void large_init(LargeJob J) {
         s->nR = rz ? M : nB;
         s->nC = rz ? (nA < nB ? nA : nB) : nA;
         s->M = rz ? M : 0;
-        s->ntiles = ok ? tiles_of(s->nC, s->nR) : 0;
+        s->ntiles = !ok ? 0 : (J.strips ? (s->nC + strips::kRows - 1) / strips::kRows : tiles_of(s->nC, s->nR));
         s->active = (ok && pos[0] && pos[1]) ? 1 : 0;
         s->status = !ok ? CFSIM_INVALID_INPUT : (s->active ? 0u : (unsigned)CFSIM_DEGENERATE);
         s->final_step = 0;
@@ -171,6 +172,7 @@ __global__ __launch_bounds__(256) void large_init(LargeJob J) {
     const bool swap = rz && nB < nA;
     const GraphRef& Rg = swap ? A : B;
     const GraphRef& Cg = swap ? B : A;
+    if (J.strips) return;  // strip_build
     NodeRec<T>* rr = recs_of<T>(J, p, 0);
     NodeRec<T>* cr = recs_of<T>(J, p, 1);
     for (int v = threadIdx.x; v < Rg.n; v += 256) rr[v] = make_rec<T>(Rg, v);
@@ -530,6 +532,214 @@ __global__ __launch_bounds__(kStepThreads) void large_step(LargeJob J, int k) {
     }
 }
 
+// ---------------------------------------------------------------- strips
+// Plain pairs (calls without resize): the iterates are kept as X = S^T, n_A
+// rows of n_B entries, and launch k (1 .. max_iter + 1) takes strips of four
+// rows of all pairs (strips.h): source rows read once per strip and added by
+// FP32 matrix instructions, neighbours gathered from LDS.  The terms of an
+// entry are added in the order of large_step's gathers: the same bits.
+//
+// Bound by the latency of a strip's two stages with two workgroups per CU
+// (64 KB of LDS for 2,048 columns): 70 us per launch for 8 FP32 pairs of
+// 512-2048 nodes, against 165 us on the gathers of large_step.  With 1,024
+// threads (64 registers per lane) the column loop spills: 254 us; with the
+// long rows' call inside the loop 118 us.
+constexpr int kStripDP = kLP;
+
+template <typename T>
+__device__ inline unsigned char* strip_base(const LargeJob& J, int p) {
+    return J.strip_area + (long long)p * J.strip_stride;
+}
+template <typename T>
+__host__ __device__ inline size_t strip_cols_bytes(int max_nodes) {
+    return align16(strips::cols_bytes<T>(max_nodes, kStripDP));
+}
+
+// Column lists and strip tables of the active pairs.
+template <typename T>
+__global__ __launch_bounds__(256) void strip_build(LargeJob J) {
+    for (int p = blockIdx.y; p < J.n_pairs; p += gridDim.y) {
+        const LargeState* s = J.st + p;
+        if (!s->active) continue;
+        GraphRef A, B;
+        pair_graphs(J, p, &A, &B);
+        const int tid = blockIdx.x * 256 + threadIdx.x, nt = gridDim.x * 256;
+        unsigned char* base = strip_base<T>(J, p);
+        const strips::Cols<T> cols = strips::carve_cols<T>(base, s->nR, kStripDP);
+        for (int i = tid; i < cols.stride; i += nt) strips::build_col<T, kStripDP>(B, i, cols);
+        strips::StripTab<T>* tabs = reinterpret_cast<strips::StripTab<T>*>(base + strip_cols_bytes<T>(J.max_nodes));
+        for (int t = tid; t < s->ntiles; t += nt)
+            strips::build_strip<T, kStripDP>(A, t * strips::kRows, s->nR, tabs + t);
+    }
+}
+
+// Rest of column i's lists past the slots, as one sum beside the slots' sum.
+template <typename T>
+__device__ inline strips::Quad<T> col_lists_rest(const GraphRef& R, int i, const strips::Quad<T>* P1,
+                                                 const strips::Quad<T>* P2) {
+    strips::Quad<T> y{};
+    for (int e = R.rp[i] + kLS; e < R.rp[i + 1]; ++e) {
+        const strips::Quad<T> g = P1[R.ci[e]];
+        for (int r = 0; r < strips::kRows; ++r) y.v[r] = dev::fma_t(T(R.w[e]), g.v[r], y.v[r]);
+    }
+    for (int e = R.cp[i] + kLP; e < R.cp[i + 1]; ++e) {
+        const strips::Quad<T> g = P2[R.ri[e]];
+        for (int r = 0; r < strips::kRows; ++r) y.v[r] = dev::fma_t(T(R.w[R.eid[e]]), g.v[r], y.v[r]);
+    }
+    return y;
+}
+
+// Terms of row c of X (node c of C) with c's list entries past the slots, for
+// column i (col_rest with the roles of lanes and rows exchanged).
+template <typename T>
+__device__ inline T long_row_rest(const T* X, int nR, const GraphRef& R, const GraphRef& C, int i, int c) {
+    T acc = T(0);
+    const int sb = C.rp[c], ns = C.rp[c + 1] - sb, pb = C.cp[c], np = C.cp[c + 1] - pb;
+    if (ns > kLS)
+        for (int e = R.rp[i]; e < R.rp[i + 1]; ++e) {
+            T in = T(0);
+            for (int q = kLS; q < ns; ++q)
+                in = dev::fma_t(T(C.w[sb + q]), X[(long long)C.ci[sb + q] * nR + R.ci[e]], in);
+            acc = dev::fma_t(T(R.w[e]), in, acc);
+        }
+    if (np > kLP)
+        for (int e = R.cp[i]; e < R.cp[i + 1]; ++e) {
+            T in = T(0);
+            for (int q = kLP; q < np; ++q)
+                in = dev::fma_t(T(C.w[C.eid[pb + q]]), X[(long long)C.ri[pb + q] * nR + R.ri[e]], in);
+            acc = dev::fma_t(T(R.w[R.eid[e]]), in, acc);
+        }
+    return acc;
+}
+
+// Adds those terms to the flagged rows of a strip, which the lane has just
+// written without them; returns the rows' nu^2.  Out of line and after the
+// other rows, so that the loop over the columns holds no call.
+template <typename T>
+__device__ __noinline__ double long_rows_add(const T* X, T* dst, int nR, int nC, int c0, int long_rows, GraphRef R,
+                                             GraphRef C, T sig, int ch0, int step) {
+    double nu2 = 0.0;
+    for (int ch = ch0; ch * kWave < nR; ch += step) {
+        const int i = ch * kWave + (int)(threadIdx.x & (kWave - 1));
+        if (i >= nR) continue;
+        for (int r = 0; r < strips::kRows; ++r) {
+            if (!((long_rows >> r) & 1) || c0 + r >= nC) continue;
+            T* at = dst + (long long)(c0 + r) * nR + i;
+            const T v = dev::fma_t(long_row_rest<T>(X, nR, R, C, i, c0 + r), sig, *at);
+            *at = v;
+            nu2 += (double)v * (double)v;
+        }
+    }
+    return nu2;
+}
+
+constexpr int kLargeStripThreads = 512;
+
+template <typename T>
+__global__ __launch_bounds__(kLargeStripThreads)
+void large_strip(LargeJob J, int k) {
+    using namespace strips;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int NW = kLargeStripThreads / kWave;
+    __shared__ double red[2 * NW];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = uni((int)threadIdx.x / kWave);
+    const bool compute = k <= J.max_iter, want_delta = (k & 1) && k >= 3;
+    const TileRange tr = tile_range(J);
+    for (long long t = tr.first; t < tr.end; t += tr.stride) {
+        const int p = uni(pair_of_tile(J, t));
+        const LargeState* s = J.st + p;
+        if (!uni(s->active)) continue;
+        const int strip = (int)(t - J.tile_off[p]), c0 = strip * kRows;
+        const int nR = uni(s->nR), nC = uni(s->nC), nch = (nR + kWave - 1) / kWave;
+        const T* src = buf_of<T>(J, p, (k - 1) & 3);
+        T* dst = buf_of<T>(J, p, k & 3);
+        const T* old = buf_of<T>(J, p, (k - 3) & 3);
+        const T c0v = T(1.0 / sqrt((double)s->nA * (double)s->nB));
+        const T sig = T(1.0 / s->nu_k[(k - 1) & 3]);   // sigma_{k-1} (1 for S_0)
+        const T sig3 = T(1.0 / s->nu_k[(k - 3) & 3]);  // sigma_{k-3}
+        GraphRef A, B;
+        pair_graphs(J, p, &A, &B);
+        unsigned char* base = strip_base<T>(J, p);
+        const StripTab<T>* tab = reinterpret_cast<const StripTab<T>*>(base + strip_cols_bytes<T>(J.max_nodes)) + strip;
+        Quad<T>* P1 = reinterpret_cast<Quad<T>*>(smem);
+        Quad<T>* P2 = P1 + col_stride(nR) + 1;
+        double nu2 = 0.0, d2 = 0.0;
+        if (compute && k > 1) {
+            __syncthreads();  // the strip before has been gathered
+            stage_sources<NW>(src, nR, tab, P1, P2);
+            __syncthreads();
+        }
+        const Cols<T> cols = carve_cols<T>(base, nR, kStripDP);
+        const int long_rows = uni(tab->long_rows);
+        for (int ch = wave; ch < nch; ch += NW) {
+            const int i = ch * kWave + lane;
+            const bool valid = i < nR;
+            if (compute && k > 1) {
+                Quad<T> y = gather_col<T, kStripDP>(cols, i, P1, P2, false, B);
+                const bool lng = valid && (B.rp[i + 1] - B.rp[i] > kLS || B.cp[i + 1] - B.cp[i] > kLP);
+                if (__ballot(lng) != 0 && lng) {
+                    const Quad<T> rest = col_lists_rest<T>(B, i, P1, P2);
+#pragma unroll
+                    for (int r = 0; r < kRows; ++r) y.v[r] += rest.v[r];
+                }
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    if (!valid || c0 + r >= nC) continue;
+                    const T v = y.v[r] * sig;
+                    dst[(long long)(c0 + r) * nR + i] = v;
+                    if (!((long_rows >> r) & 1)) nu2 += (double)v * (double)v;
+                }
+            } else if (compute) {
+                // Y_1[i][c] = c0 (outw_B(i) outw_A(c) + inw_B(i) inw_A(c))
+                T rb = T(0), qb = T(0);
+                if (valid) {
+                    for (int e = B.rp[i]; e < B.rp[i + 1]; ++e) rb += T(B.w[e]);
+                    for (int e = B.cp[i]; e < B.cp[i + 1]; ++e) qb += T(B.w[B.eid[e]]);
+                }
+                for (int r = 0; r < kRows; ++r) {
+                    const int c = c0 + r;
+                    if (c >= nC) break;
+                    T ra = T(0), qa = T(0);
+                    for (int e = A.rp[c]; e < A.rp[c + 1]; ++e) ra += T(A.w[e]);
+                    for (int e = A.cp[c]; e < A.cp[c + 1]; ++e) qa += T(A.w[A.eid[e]]);
+                    const T acc = c0v * (rb * ra + qb * qa);
+                    if (valid) {
+                        dst[(long long)c * nR + i] = acc;
+                        nu2 += (double)acc * (double)acc;
+                    }
+                }
+            }
+            if (want_delta) {
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    if (!valid || c0 + r >= nC) continue;
+                    const long long o = (long long)(c0 + r) * nR + i;
+                    const T a = T(src[o] * sig);                       // S_{k-1}
+                    const T b = k == 3 ? c0v : T(old[o] * sig3);       // S_{k-3}
+                    const double d = (double)a - (double)b;
+                    d2 += d * d;
+                }
+            }
+        }
+        if (long_rows && compute && k > 1)
+            nu2 += long_rows_add<T>(src, dst, nR, nC, c0, long_rows, B, A, sig, wave, NW);
+        nu2 = wave_sum(nu2);
+        d2 = wave_sum(d2);
+        __syncthreads();  // red of the strip before has been read
+        if (lane == 0) {
+            red[wave] = nu2;
+            red[NW + wave] = d2;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double a = 0.0;
+            for (int w = 0; w < NW; ++w) a += red[threadIdx.x * NW + w];
+            (threadIdx.x ? J.part_delta : J.part_nu)[t] = a;
+        }
+    }
+}
+
 // ---------------------------------------------------------------- resize: G, norms
 // Launch k (0 .. max_iter + 1) for resized pairs: V_k = U_k G (k <= max_iter;
 // U_0 is the constant 1/M), nu_k^2 = <U_k, V_k> (k >= 1), and at odd k >= 3
@@ -629,6 +839,11 @@ __device__ inline FinalBufs<T> final_bufs(const LargeJob& J, int p, const LargeS
     b.nC = rz ? s->M : s->nA;   // columns of S (A side)
     b.S = rz ? buf_of<T>(J, p, kSlotS) : buf_of<T>(J, p, f & 3);
     b.St = rz ? buf_of<T>(J, p, kSlotU + ((f + 1) & 3)) : buf_of<T>(J, p, (f + 1) & 3);
+    if (J.strips) {  // the iterate is S^T
+        T* x = b.S;
+        b.S = b.St;
+        b.St = x;
+    }
     b.lists = reinterpret_cast<uint16_t*>(rz ? buf_of<T>(J, p, kSlotU + ((f + 2) & 3)) : buf_of<T>(J, p, (f + 2) & 3));
     return b;
 }
@@ -653,6 +868,26 @@ __global__ __launch_bounds__(kFinalThreads) void large_final(LargeJob J) {
     const int ntc = (nC + 31) / 32, ntiles = ((nR + 31) / 32) * ntc;
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int i0 = (t / ntc) * 32, j0 = (t % ntc) * 32;
+        if (J.strips) {  // S^T scaled in place, S from it
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int c = j0 + ty + 8 * k, r = i0 + tx;
+                if (c < nC && r < nR) {
+                    const long long o = (long long)c * nR + r;
+                    const T v = f == 0 ? c0v : fb.St[o] * sigT;
+                    fb.St[o] = v;
+                    tile[ty + 8 * k][tx] = v;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = i0 + ty + 8 * k, j = j0 + tx;
+                if (i < nR && j < nC) fb.S[(long long)i * nC + j] = tile[tx][ty + 8 * k];
+            }
+            __syncthreads();
+            continue;
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int i = i0 + ty + 8 * k, j = j0 + tx;
@@ -991,8 +1226,23 @@ size_t large_sort_lds(int max_nodes, int esize) {
     return (size_t)(P > kSortElems ? P : kSortElems) * (esize == 8 ? 12 : 8);
 }
 
+size_t large_strip_bytes(int max_nodes, int esize) {
+    const size_t n = (max_nodes + strips::kRows - 1) / strips::kRows;
+    return esize == 8 ? strip_cols_bytes<double>(max_nodes) + n * sizeof(strips::StripTab<double>)
+                      : strip_cols_bytes<float>(max_nodes) + n * sizeof(strips::StripTab<float>);
+}
+
+constexpr size_t kStripLdsMax = 158 * 1024;
+bool large_on_strips(int max_nodes, int esize) {
+    return (esize == 8 ? strips::strip_lds<double>(max_nodes) : strips::strip_lds<float>(max_nodes)) <= kStripLdsMax;
+}
+
 int set_large_attributes() {
     int e = 0;
+    e |= (int)hipFuncSetAttribute(reinterpret_cast<const void*>(&large_strip<float>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripLdsMax);
+    e |= (int)hipFuncSetAttribute(reinterpret_cast<const void*>(&large_strip<double>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripLdsMax);
     e |= (int)hipFuncSetAttribute(reinterpret_cast<const void*>(&large_finish<float>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
     e |= (int)hipFuncSetAttribute(reinterpret_cast<const void*>(&large_finish<double>),
@@ -1047,6 +1297,22 @@ static int launch_large_t(const LargeJob& J, int grid, hipStream_t stream) {
         if ((e = launch_mfma_prep(J, stream)) != 0) return e;
         for (int k = 1; k <= J.max_iter + 1; ++k) {
             if ((e = launch_mfma_update(J, k, ggrid, stream)) != 0) return e;
+            hipLaunchKernelGGL(large_reduce, dim3(J.n_pairs < kReduceGrid ? J.n_pairs : kReduceGrid), dim3(kStepThreads), 0,
+                               stream, J, k);
+            if ((e = (int)hipGetLastError()) != 0) return e;
+        }
+        return launch_finish<T>(J, stream);
+    }
+    if (J.strips) {  // plain pairs: one launch over strips, one reduction per update
+        hipLaunchKernelGGL(strip_build<T>, dim3(16, J.n_pairs < 1024 ? J.n_pairs : 1024), dim3(256), 0, stream, J);
+        if ((e = (int)hipGetLastError()) != 0) return e;
+        long long sg = (long long)J.n_pairs * ((J.max_nodes + strips::kRows - 1) / strips::kRows);
+        sg = sg < 8ll * grid ? sg : 8ll * grid;
+        const int sgrid = (int)((sg + 7) / 8 * 8);
+        const size_t lds = strips::strip_lds<T>(J.max_nodes);
+        for (int k = 1; k <= J.max_iter + 1; ++k) {
+            hipLaunchKernelGGL(large_strip<T>, dim3(sgrid), dim3(kLargeStripThreads), lds, stream, J, k);
+            if ((e = (int)hipGetLastError()) != 0) return e;
             hipLaunchKernelGGL(large_reduce, dim3(J.n_pairs < kReduceGrid ? J.n_pairs : kReduceGrid), dim3(kStepThreads), 0,
                                stream, J, k);
             if ((e = (int)hipGetLastError()) != 0) return e;

@@ -499,7 +499,7 @@ __device__ __forceinline__ IterOut iterate_strips(const PairJob& J, const PairSh
                     if (long_rows)
                         for (int r = 0; r < kRows; ++r)
                             if (((long_rows >> r) & 1) && valid) {
-                                const T add = long_row_terms<T>(Xc, nR, R, C, i, c0 + r);
+                                const T add = long_row_call<T>(Xc, nR, R, C, i, c0 + r);
 #pragma unroll
                                 for (int z = 0; z < kRows; ++z) y.v[z] += z == r ? add : T(0);
                             }

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
     const StripTab<T>* tab = reinterpret_cast<const StripTab<T>*>(S.tabs) + strip;
     Quad<T>* P1 = reinterpret_cast<Quad<T>*>(smem);
     Quad<T>* P2 = P1 + col_stride(nR) + 1;
-    stage_sources<T>(Xc, nR, tab, P1, P2);
+    stage_sources<kWaves>(Xc, nR, tab, P1, P2);
     const StripState st = state_after(S, k - 1);
     if (strip == 0 && threadIdx.x == 0) S.st[(k - 1) & 1] = st;
     if (st.status != 0) return;  // the same in every thread
@@ -129,17 +129,9 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
             old[r] = even && valid && c0 + r < nC ? Xn[(long long)(c0 + r) * nR + i] : T(0);
         const bool lng = valid && (R.rp[i + 1] - R.rp[i] > 2 || R.cp[i + 1] - R.cp[i] > kDP);
         Quad<T> y = gather_col<T, kDP>(cols, i, P1, P2, __ballot(lng) != 0, R);
-        if (long_rows) {
-            for (int r = 0; r < kRows; ++r)
-                if (((long_rows >> r) & 1) && valid) {
-                    const T add = long_row_terms<T>(Xc, nR, R, C, i, c0 + r);
-#pragma unroll
-                    for (int s = 0; s < kRows; ++s) y.v[s] += s == r ? add : T(0);
-                }
-        }
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
-            if (!valid || c0 + r >= nC) continue;
+            if (!valid || c0 + r >= nC || ((long_rows >> r) & 1)) continue;
             const T f = y.v[r] * sigma;
             Xn[(long long)(c0 + r) * nR + i] = f;
             v[0] += (double)f * (double)f;
@@ -149,6 +141,13 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
                 v[2] += dy * (double)f;
             }
         }
+    }
+    if (long_rows) {
+        const RowSums ls = long_rows_pass<T, kDP>(Xc, Xn, nR, nC, c0, long_rows, S.cols, P1, P2, R, C, sigma, even, wave,
+                                                  kWaves);
+        v[0] += ls.nu2;
+        v[1] += ls.dy2;
+        v[2] += ls.dyy;
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) v[a] = wave_sum(v[a]);

@@ -1,4 +1,4 @@
-"""Plain pairs past LDS on strips against the one-workgroup kernel and the oracle.
+"""Plain pairs on strips: past LDS against the one-workgroup kernel, large pairs against the oracle.
 
 Both kernels add an entry's terms in the same order; only the FP64 norm sums
 are grouped differently (relative 1e-15), so S agrees to a few roundings of
@@ -74,3 +74,20 @@ def test_strips_converge_and_stop_like_the_oracle(cf, ctx):
     ref = oracle_pair(graphs, 0, 1, tol=1e-3)
     assert got["iters"] == ref.iters and (got["status"] & 15) == ref.status
     check_matching(got["S"], got["match"], ref.S, "f64")
+
+
+@pytest.mark.parametrize("dtype,tol", [("f32", 1e-5), ("f64", 1e-10)])
+@pytest.mark.parametrize("kind,max_iter", [("cfg", 20), ("wide", 20), ("wide", 1), ("wide", 2), ("wide", 3),
+                                           ("empty", 4)])
+def test_large_pairs_of_unequal_sizes_on_strips(cf, ctx, kind, max_iter, dtype, tol):
+    sizes = [(6, 9), (64, 65), (257, 130), (131, 511)]
+    graphs = [g for nA, nB in sizes for g in _pair(nA, nB, kind)]
+    gs = cf.pack(ctx, graphs)
+    pa, pb = [0, 2, 4, 6, 6], [1, 3, 5, 7, 2]
+    res, match, S = cf.score_batch(ctx, gs, pa, pb, dtype=dtype, max_iter=max_iter, tol=0.0, want_S=True,
+                                   path="large")
+    for q, (a, b) in enumerate(zip(pa, pb)):
+        ref = oracle_pair(graphs, a, b, max_iter=max_iter, tol=0.0)
+        assert S[q].shape == ref.S.shape and rel_err(S[q], ref.S) <= tol
+        assert res["iters"][q] == ref.iters and (res["status"][q] & 15) == ref.status
+        check_matching(S[q], match[q], ref.S, dtype)
