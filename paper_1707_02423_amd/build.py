@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["csrc/pair_resized_f32.hip", "csrc/pair_resized_f64.hip", "csrc/pair_plain_f32.hip",
            "csrc/pair_plain_f64.hip", "csrc/pair_damped_f32.hip", "csrc/pair_damped_f64.hip",
            "csrc/strips.hip", "csrc/api.hip", "csrc/pack.hip", "csrc/pair.hip",
-           "csrc/topk.hip", "csrc/adjoint.hip", "csrc/large.hip",
+           "csrc/topk.hip", "csrc/adjoint.hip", "csrc/adjoint_strips.hip", "csrc/large.hip",
            "csrc/large_mfma.hip", "csrc/distances.hip", "csrc/assign.hip",
            "csrc/ward.hip"]
 LIB = os.path.join(HERE, "libcfsim.so")

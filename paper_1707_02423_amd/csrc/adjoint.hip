@@ -14,18 +14,15 @@
 // before it is walked backwards.  One workgroup per pair; S, Ybar and Gbar
 // live in a workspace slot (L2-resident), lists and gradient accumulators in
 // LDS; gradients are added to grad_w with FP64 atomics (graphs may be shared).
-#include "cfsim_internal.h"
-#include "pair_device.h"
+// Calls of few pairs that have the forward's checkpoints run on strips
+// (adjoint_strips.hip), except the pairs which that path does not take.
+#include "adjoint_job.h"
 
 namespace cfsim {
 
 namespace {
 
 using namespace dev;
-
-constexpr int kBwdThreads = 512;
-constexpr int kBwdLds = 78 * 1024;
-constexpr int kAChunks = 8;  // A edges held by the lanes (64 per chunk) in the lane-parallel edge sums
 
 template <typename T>
 __device__ inline T* slot_buf(T* base, long long slot_elems, int b) {
@@ -61,25 +58,6 @@ __device__ double apply_M(const T* src, T* dst, T scale, const PairShape& sh, co
     return block_sum<NW>(nu2, red);
 }
 
-struct BwdJob {
-    SetRef set;
-    const int32_t* pair_a;
-    const int32_t* pair_b;
-    int n_pairs;
-    const cfsim_pair_result* fwd;
-    const int32_t* match;
-    const int64_t* match_off;
-    const double* grad_score;
-    double* grad_w;
-    int32_t* pair_status;  // optional: 0 done, CFSIM_INVALID_INPUT skipped
-    int ckpt, max_iter;
-    const void* fck;       // forward checkpoints (NULL: the forward is recomputed here)
-    const int64_t* fck_off;
-    void* ws;              // gridDim.x slots of slot_bytes
-    long long slot_elems, slot_bytes;
-    int32_t* queue;
-};
-
 __host__ __device__ inline int n_ckpt(int max_iter, int ckpt) { return max_iter / ckpt + 1; }
 
 template <typename T>
@@ -88,27 +66,24 @@ __device__ void backward_pair(const BwdJob& J, int p, unsigned char* smem, doubl
     constexpr int NW = NT / kWave;
     const int tid = threadIdx.x;
     int32_t st = CFSIM_INVALID_INPUT;
-    const int ga = J.pair_a[p], gb = J.pair_b[p];
-    const cfsim_pair_result fr = J.fwd[p];
-    const int K = fr.iters;
-    bool ok = ga >= 0 && ga < J.set.n_graphs && gb >= 0 && gb < J.set.n_graphs && K >= 0 && K <= J.max_iter &&
-              !(fr.status & CFSIM_INVALID_INPUT);
     GraphRef A{}, B{};
+    BwdShape bs{};
     PairShape sh{};
-    size_t lists_bytes = 0;
+    bool ok = bwd_pair(J, p, &A, &B);
     if (ok) {
-        A = graph_of(J.set, ga);
-        B = graph_of(J.set, gb);
+        bs = bwd_shape(A, B, (int)sizeof(T));
+        if (J.strips && bwd_on_strips(A, B, bs)) return;
         sh = make_shape(A.n, B.n, 0, NW);  // S kept as n_B x n_A: R = B, C = A
-        lists_bytes = lds_lists_bytes(sh.nR, sh.nC, B.nnz, A.nnz, (int)sizeof(T));
-        ok = A.n >= 1 && B.n >= 1 && (long long)A.n * B.n <= J.slot_elems &&
-             lists_bytes + align16((size_t)(A.nnz + B.nnz) * 8) + align16((size_t)(A.nnz + B.nnz) * 4) <=
-                 (size_t)kBwdLds;
+        ok = bs.fits;
     }
     if (!ok) {
         if (tid == 0 && J.pair_status) J.pair_status[p] = st;
         return;
     }
+    const size_t lists_bytes = bs.lists, scratch_off = bs.scratch_off;
+    const int ga = J.pair_a[p], gb = J.pair_b[p];
+    const cfsim_pair_result fr = J.fwd[p];
+    const int K = fr.iters;
     st = 0;
     const double gs = J.grad_score[p];
     if ((fr.status & CFSIM_DEGENERATE) || K == 0 || gs == 0.0) {  // no dependence on the weights
@@ -122,8 +97,6 @@ __device__ void backward_pair(const BwdJob& J, int p, unsigned char* smem, doubl
     double* gB = gA + A.nnz;
     int* srcA = reinterpret_cast<int*>(smem + lists_bytes + align16((size_t)(A.nnz + B.nnz) * 8));
     int* srcB = srcA + A.nnz;
-    const size_t scratch_off = lists_bytes + align16((size_t)(A.nnz + B.nnz) * 8) + align16((size_t)(A.nnz + B.nnz) * 4);
-    const size_t scratch_bytes = (size_t)NW * kAChunks * kWave * sizeof(T);
 
     // workspace slot: checkpoints | segment (ckpt+1) | Ybar | Gbar | nu[max_iter]
     T* base = reinterpret_cast<T*>(static_cast<unsigned char*>(J.ws) + (size_t)blockIdx.x * J.slot_bytes);
@@ -175,7 +148,7 @@ __device__ void backward_pair(const BwdJob& J, int p, unsigned char* smem, doubl
     const int wave = uni(tid / kWave);
     const int nchA = (keptA + kWave - 1) / kWave;
     T* part = reinterpret_cast<T*>(smem + scratch_off);
-    const bool lane_edges = nchA <= kAChunks && scratch_off + scratch_bytes <= (size_t)kBwdLds;
+    const bool lane_edges = bs.lane_edges;
 
     // ---- reverse: Gbar = g * indicator(matching)
     const int64_t mo = J.match_off ? J.match_off[p] : 0;
@@ -323,7 +296,7 @@ int launch_backward(int dtype, const SetRef& set, const int32_t* pair_a, const i
                     const cfsim_pair_result* fwd, const int32_t* match, const int64_t* match_off,
                     const double* grad_score, double* grad_w, int32_t* pair_status, int ckpt,
                     const void* fck, const int64_t* fck_off, int max_iter,
-                    void* ws, long long slot_elems, int grid, hipStream_t stream) {
+                    void* ws, size_t ws_bytes, int max_nodes, long long slot_elems, int grid, hipStream_t stream) {
     BwdJob J;
     J.set = set;
     J.pair_a = pair_a;
@@ -342,12 +315,18 @@ int launch_backward(int dtype, const SetRef& set, const int32_t* pair_a, const i
     const int esize = dtype == CFSIM_F64 ? 8 : 4;
     J.slot_elems = slot_elems;
     J.slot_bytes = backward_slot_bytes(max_iter, ckpt, slot_elems, esize);
+    // the strips path where it fits the workspace of the other: the size does
+    // not depend on the route
+    const size_t strip_ws = fck ? bwd_strips_bytes(max_nodes, n_pairs, grid, ckpt, esize) : 0;
+    J.strips = strip_ws != 0 && ws_bytes >= strip_ws;
+    J.ws = ws;
+    int e = 0;
+    if (J.strips && (e = launch_bwd_strips(dtype, J, max_nodes, grid / 2, stream)) != 0) return e;
     // queue counter in front of the slots
     J.queue = static_cast<int32_t*>(ws);
     J.ws = static_cast<unsigned char*>(ws) + 256;
     hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(1), 0, stream, J.queue);
-    int e = (int)hipGetLastError();
-    if (e != 0) return e;
+    if ((e = (int)hipGetLastError()) != 0) return e;
     const void* f = dtype == CFSIM_F64 ? reinterpret_cast<const void*>(&backward_kernel<double>)
                                        : reinterpret_cast<const void*>(&backward_kernel<float>);
     e = (int)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLds);

@@ -1208,8 +1208,8 @@ cfsim_status cfsim_score_backward(cfsim_context* ctx, const cfsim_graph_set* set
     int e = (int)hipSetDevice(ctx->device);
     if (e != 0) return hip_fail(e, "hipSetDevice");
     e = cfsim::launch_backward(opt->dtype, ref_of(set), pair_a, pair_b, (int)n_pairs, fwd, match, match_off,
-                               grad_score, grad_w, pair_status, checkpoint_every, ckpt, ckpt_off, opt->max_iter, ws,
-                               global_slot_elems(set->max_nodes), cfsim::backward_grid(ctx->num_cus),
+                               grad_score, grad_w, pair_status, checkpoint_every, ckpt, ckpt_off, opt->max_iter, ws, need,
+                               set->max_nodes, global_slot_elems(set->max_nodes), cfsim::backward_grid(ctx->num_cus),
                                static_cast<hipStream_t>(stream));
     if (e != 0) return hip_fail(e, "backward launch");
     return ok();

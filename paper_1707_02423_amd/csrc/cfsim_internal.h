@@ -475,7 +475,9 @@ int launch_backward(int dtype, const SetRef& set, const int32_t* pair_a, const i
                     const cfsim_pair_result* fwd, const int32_t* match, const int64_t* match_off,
                     const double* grad_score, double* grad_w, int32_t* pair_status, int ckpt,
                     const void* fck, const int64_t* fck_off, int max_iter,
-                    void* ws, long long slot_elems, int grid, hipStream_t stream);
+                    void* ws, size_t ws_bytes, int max_nodes, long long slot_elems, int grid,
+                    hipStream_t stream);
+size_t bwd_strips_bytes(int max_nodes, long long n_pairs, int grid, int ckpt, int esize);
 
 // Top-k (topk.hip).
 long long topk_blocks(long long n);

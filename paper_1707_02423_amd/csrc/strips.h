@@ -329,35 +329,34 @@ __device__ __forceinline__ const Quad<T>& quad_at(const Quad<T>* P, int off) {
 // 4 predecessors), for column i, as the pair kernels add them: for a node i
 // within 2 successors and 3 predecessors the sum over i's slots inside the
 // sum over the rest of c's lists, else the other way round.
-template <typename T>
-__device__ inline T long_row_terms(const T* X, int nR, const GraphRef& R, const GraphRef& C, int i, int c) {
+// X(row, column) reads the iterate.
+template <typename T, typename At>
+__device__ inline T long_row_terms(At X, const GraphRef& R, const GraphRef& C, int i, int c) {
     const int sb = R.rp[i], ns = R.rp[i + 1] - sb, pb = R.cp[i], np = R.cp[i + 1] - pb;
     const int cs0 = C.rp[c] + 2, cs1 = C.rp[c + 1], cp0 = C.cp[c] + 4, cp1 = C.cp[c + 1];
     T y = T(0);
     if (ns <= 2 && np <= 3) {
         for (int q = cs0; q < cs1; ++q) {
-            const T* row = X + (long long)C.ci[q] * nR;
+            const int row = C.ci[q];
             T s = T(0);
-            for (int a = 0; a < ns; ++a) s = dev::fma_t(T(R.w[sb + a]), row[R.ci[sb + a]], s);
+            for (int a = 0; a < ns; ++a) s = dev::fma_t(T(R.w[sb + a]), X(row, R.ci[sb + a]), s);
             y = dev::fma_t(T(C.w[q]), s, y);
         }
         for (int q = cp0; q < cp1; ++q) {
-            const T* row = X + (long long)C.ri[q] * nR;
+            const int row = C.ri[q];
             T s = T(0);
-            for (int b = 0; b < np; ++b) s = dev::fma_t(T(R.w[R.eid[pb + b]]), row[R.ri[pb + b]], s);
+            for (int b = 0; b < np; ++b) s = dev::fma_t(T(R.w[R.eid[pb + b]]), X(row, R.ri[pb + b]), s);
             y = dev::fma_t(T(C.w[C.eid[q]]), s, y);
         }
     } else {
         for (int a = 0; a < ns; ++a) {
             T s = T(0);
-            for (int q = cs0; q < cs1; ++q)
-                s = dev::fma_t(T(C.w[q]), X[(long long)C.ci[q] * nR + R.ci[sb + a]], s);
+            for (int q = cs0; q < cs1; ++q) s = dev::fma_t(T(C.w[q]), X(C.ci[q], R.ci[sb + a]), s);
             y = dev::fma_t(T(R.w[sb + a]), s, y);
         }
         for (int b = 0; b < np; ++b) {
             T s = T(0);
-            for (int q = cp0; q < cp1; ++q)
-                s = dev::fma_t(T(C.w[C.eid[q]]), X[(long long)C.ri[q] * nR + R.ri[pb + b]], s);
+            for (int q = cp0; q < cp1; ++q) s = dev::fma_t(T(C.w[C.eid[q]]), X(C.ri[q], R.ri[pb + b]), s);
             y = dev::fma_t(T(R.w[R.eid[pb + b]]), s, y);
         }
     }
@@ -369,59 +368,80 @@ __device__ inline T long_row_terms(const T* X, int nR, const GraphRef& R, const 
 // for the query of 3,000 graphs).
 template <typename T>
 __device__ __noinline__ T long_row_call(const T* X, int nR, const GraphRef& R, const GraphRef& C, int i, int c) {
-    return long_row_terms<T>(X, nR, R, C, i, c);
+    return long_row_terms<T>([=](int v, int u) { return X[(long long)v * nR + u]; }, R, C, i, c);
+}
+
+// One column's slots.
+template <typename T, int DP>
+struct ColSlots {
+    int so[2], po[DP];
+    T sw[2], pw[DP];
+};
+template <typename T, int DP>
+__device__ __forceinline__ ColSlots<T, DP> load_col(const Cols<T>& c, int i) {
+    ColSlots<T, DP> k;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        k.so[q] = c.so[q * c.stride + i];
+        k.sw[q] = c.sw[q * c.stride + i];
+    }
+#pragma unroll
+    for (int q = 0; q < DP; ++q) {
+        k.po[q] = c.po[q * c.stride + i];
+        k.pw[q] = c.pw[q * c.stride + i];
+    }
+    return k;
 }
 
 // Stage B for one column (DP predecessor slots): the terms of its slots and,
 // when `rest` (some lane's lists are longer), those of longer lists, in list
-// order, successors before predecessors.
+// order, successors before predecessors; graph() is the R graph.
+template <typename T, int DP, typename Graph>
+__device__ __forceinline__ Quad<T> gather_slots(const ColSlots<T, DP>& k, int i, const Quad<T>* P1,
+                                                const Quad<T>* P2, bool rest, const Graph& graph) {
+    Quad<T> y;
+    {
+        const Quad<T> g = quad_at(P1, k.so[0]);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) y.v[r] = k.sw[0] * g.v[r];
+    }
+    {
+        const Quad<T> g = quad_at(P1, k.so[1]);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(k.sw[1], g.v[r], y.v[r]);
+    }
+    if (rest) {
+        const GraphRef R = graph();
+        if (i < R.n)
+            for (int e = R.rp[i] + 2; e < R.rp[i + 1]; ++e) {
+                const Quad<T> g = P1[R.ci[e]];
+                const T w = T(R.w[e]);
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(w, g.v[r], y.v[r]);
+            }
+    }
+#pragma unroll
+    for (int q = 0; q < DP; ++q) {
+        const Quad<T> g = quad_at(P2, k.po[q]);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(k.pw[q], g.v[r], y.v[r]);
+    }
+    if (rest) {
+        const GraphRef R = graph();
+        if (i < R.n)
+            for (int e = R.cp[i] + DP; e < R.cp[i + 1]; ++e) {
+                const Quad<T> g = P2[R.ri[e]];
+                const T w = T(R.w[R.eid[e]]);
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(w, g.v[r], y.v[r]);
+            }
+    }
+    return y;
+}
 template <typename T, int DP>
 __device__ __forceinline__ Quad<T> gather_col(const Cols<T>& c, int i, const Quad<T>* P1, const Quad<T>* P2,
                                               bool rest, const GraphRef& R) {
-    Quad<T> y;
-    int so[2], po[DP];
-    T sw[2], pw[DP];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        so[q] = c.so[q * c.stride + i];
-        sw[q] = c.sw[q * c.stride + i];
-    }
-#pragma unroll
-    for (int q = 0; q < DP; ++q) {
-        po[q] = c.po[q * c.stride + i];
-        pw[q] = c.pw[q * c.stride + i];
-    }
-    {
-        const Quad<T> g = quad_at(P1, so[0]);
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) y.v[r] = sw[0] * g.v[r];
-    }
-    {
-        const Quad<T> g = quad_at(P1, so[1]);
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(sw[1], g.v[r], y.v[r]);
-    }
-    if (rest && i < R.n)
-        for (int e = R.rp[i] + 2; e < R.rp[i + 1]; ++e) {
-            const Quad<T> g = P1[R.ci[e]];
-            const T w = T(R.w[e]);
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(w, g.v[r], y.v[r]);
-        }
-#pragma unroll
-    for (int q = 0; q < DP; ++q) {
-        const Quad<T> g = quad_at(P2, po[q]);
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(pw[q], g.v[r], y.v[r]);
-    }
-    if (rest && i < R.n)
-        for (int e = R.cp[i] + DP; e < R.cp[i + 1]; ++e) {
-            const Quad<T> g = P2[R.ri[e]];
-            const T w = T(R.w[R.eid[e]]);
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) y.v[r] = dev::fma_t(w, g.v[r], y.v[r]);
-        }
-    return y;
+    return gather_slots<T, DP>(load_col<T, DP>(c, i), i, P1, P2, rest, [&] { return R; });
 }
 
 // The rows of a strip whose lists are longer than the slots, by the pair
@@ -449,7 +469,8 @@ __device__ __noinline__ RowSums long_rows_pass(const T* Xc, T* Xn, int nR, int n
 #pragma unroll
             for (int q = 0; q < kRows; ++q)
                 if (q == r) z = y.v[q];
-            const T f = (z + long_row_terms<T>(Xc, nR, R, C, i, c0 + r)) * sigma;
+            const auto at_X = [=](int v, int u) { return Xc[(long long)v * nR + u]; };
+            const T f = (z + long_row_terms<T>(at_X, R, C, i, c0 + r)) * sigma;
             T* at = Xn + (long long)(c0 + r) * nR + i;
             if (even) {
                 const double dy = (double)f - (double)*at;
