@@ -866,6 +866,7 @@ __global__ __launch_bounds__(kFinalThreads) void large_final(LargeJob J) {
     const int m = s->nC, M = s->M;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const int ntc = (nC + 31) / 32, ntiles = ((nR + 31) / 32) * ntc;
+    T* So = J.S_out ? reinterpret_cast<T*>(J.S_out) + (J.S_off ? J.S_off[p] : 0) : nullptr;
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int i0 = (t / ntc) * 32, j0 = (t % ntc) * 32;
         if (J.strips) {  // S^T scaled in place, S from it
@@ -883,7 +884,11 @@ __global__ __launch_bounds__(kFinalThreads) void large_final(LargeJob J) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int i = i0 + ty + 8 * k, j = j0 + tx;
-                if (i < nR && j < nC) fb.S[(long long)i * nC + j] = tile[tx][ty + 8 * k];
+                if (i < nR && j < nC) {
+                    const T v = tile[tx][ty + 8 * k];
+                    fb.S[(long long)i * nC + j] = v;
+                    if (So) So[(long long)i * nC + j] = v;
+                }
             }
             __syncthreads();
             continue;
@@ -911,6 +916,7 @@ __global__ __launch_bounds__(kFinalThreads) void large_final(LargeJob J) {
                     v = T(y);
                 }
                 fb.S[(long long)i * nC + j] = v;
+                if (So) So[(long long)i * nC + j] = v;
                 tile[ty + 8 * k][tx] = v;
             }
         }
@@ -1063,37 +1069,137 @@ __global__ __launch_bounds__(kSortThreads) void large_sort_lines(LargeJob J) {
     }
 }
 
-// First position >= q of a sorted line (n entries) whose partner is free
-// (state -1), and that partner in y; n and -1 if none.  The entries are read
-// W at a time: 8 for the first step (the partner is usually among them), 32
-// (about one cache line) after that, so a long run of taken partners costs
-// few load latencies.
+// W entries of a sorted line (n entries) from position q on, or its last W.
+// Eight entries are one 16-byte read (lines start at any even address).
 template <int W>
-__device__ inline int free_in_step(const uint16_t* line, int q, int n, const int* state, int& y) {
-    int v[W];
+struct LineStep {
+    uint32_t e[W / 2];
+    int first;
+
+    __device__ __forceinline__ void read(const uint16_t* line, int q, int n) {
+        first = n >= W ? min(q, n - W) : 0;
+        if (n >= W) {
+            __builtin_memcpy(e, line + first, sizeof(e));
+        } else {
 #pragma unroll
-    for (int a = 0; a < W; ++a) v[a] = q + a < n ? line[q + a] : 0;
-    int hit = -1;
+            for (int a = 0; a < W / 2; ++a)
+                e[a] = (2 * a < n ? (uint32_t)line[2 * a] : 0u) | (2 * a + 1 < n ? (uint32_t)line[2 * a + 1] << 16 : 0u);
+        }
+    }
+    // first position >= q in the step whose partner is free (state -1), with
+    // the partner in y; -1 if none
+    __device__ __forceinline__ int free_from(int q, int n, const int* state, int& y) const {
+        int hit = -1;
 #pragma unroll
-    for (int a = W - 1; a >= 0; --a)
-        if (q + a < n && state[v[a]] == -1) hit = a;
-    if (hit >= 0) y = v[hit];
-    return hit;
+        for (int a = W - 1; a >= 0; --a) {
+            const int v = (int)(a & 1 ? e[a / 2] >> 16 : e[a / 2] & 0xffffu);
+            if (first + a >= q && first + a < n && state[v] == -1) {
+                hit = first + a;
+                y = v;
+            }
+        }
+        return hit;
+    }
+};
+
+// A line whose best partner was taken: its next free one.  begin() issues the
+// read of the first 8 entries (the partner is usually among them), end() reads
+// on 32 at a time, so that a thread's lines are read together and a long run
+// of taken partners costs few load latencies.
+struct LineSearch {
+    LineStep<8> step;
+    const uint16_t* line;
+    int q, n;
+    bool on;
+
+    __device__ __forceinline__ void begin(const uint16_t* at, int pos, int len) {
+        line = at;
+        q = pos;
+        n = len;
+        on = true;
+        if (q < n) step.read(line, q, n);
+    }
+    __device__ __forceinline__ void end(const int* state, uint16_t* pos, int16_t* best) {
+        if (!on) return;
+        int y = -1, at = n;
+        if (q < n) {
+            int h = step.free_from(q, n, state, y);
+            for (q += 8; h < 0 && q < n; q += 32) {
+                LineStep<32> s;
+                s.read(line, q, n);
+                h = s.free_from(q, n, state, y);
+            }
+            if (h >= 0)
+                at = h;
+            else
+                y = -1;
+        }
+        *pos = (uint16_t)at;
+        *best = (int16_t)y;
+    }
+};
+
+// The margin of a pair whose S has at least 2^16 entries is taken by
+// workgroups of their own after the matching, which leaves its picks in a free
+// slot: picked values | partner of every line | one partial minimum per
+// workgroup.  Smaller pairs (and any whose slot is too short) do it in
+// large_finish.  One workgroup read the S of 8 pairs of 512-2048 nodes, and
+// wrote it out, in 2.4 of 6.4 ms.
+constexpr int kMarginThreads = 256;
+constexpr int kMarginBlocks = 64;
+constexpr long long kMarginSpread = 1 << 16;
+
+template <typename T>
+struct MarginArea {
+    T* pv;
+    int* partner;
+    double* part;
+    bool spread;
+};
+template <typename T>
+__device__ inline MarginArea<T> margin_area(const LargeJob& J, int p, const LargeState* s, int nR, int nC) {
+    T* at = s->rz ? buf_of<T>(J, p, kSlotV) : buf_of<T>(J, p, (s->final_step + 3) & 3);
+    const long long lines = (nR + nC + 3) & ~3;  // keeps what follows aligned (slots are)
+    MarginArea<T> a;
+    a.pv = at;
+    a.partner = reinterpret_cast<int*>(at + lines);
+    a.part = reinterpret_cast<double*>(a.partner + lines);
+    a.spread = (long long)nR * nC >= kMarginSpread && ((size_t)at & 7) == 0 &&
+               lines * (long long)(sizeof(T) + 4) + kMarginBlocks * 8 <= J.slot_elems * (long long)sizeof(T);
+    return a;
 }
 
-__device__ inline int first_free(const uint16_t* line, int q, int n, const int* state, int& y) {
-    if (q < n) {
-        const int h = free_in_step<8>(line, q, n, state, y);
-        if (h >= 0) return q + h;
-        q += 8;
+template <typename T>
+__global__ __launch_bounds__(kMarginThreads) void large_margin(LargeJob J) {
+    __shared__ double red[kMarginThreads / kWave];
+    const int p = blockIdx.y;
+    const LargeState* s = J.st + p;
+    if (s->status & CFSIM_INVALID_INPUT) return;
+    const FinalBufs<T> fb = final_bufs<T>(J, p, s);
+    const MarginArea<T> a = margin_area<T>(J, p, s, fb.nR, fb.nC);
+    if (!a.spread) return;
+    constexpr int NW = kMarginThreads / kWave;
+    const int wave = uni((int)threadIdx.x / kWave);
+    const double m = dev::block_min<NW>(
+        dev::margin_rows<T>(fb.S, fb.nR, fb.nC, false, a.partner, a.partner + fb.nR, a.pv, a.pv + fb.nR,
+                            blockIdx.x * NW + wave, gridDim.x * NW),
+        red);
+    if (threadIdx.x == 0) a.part[blockIdx.x] = m;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kWave) void large_margin_done(LargeJob J, int blocks) {
+    const int p = blockIdx.x;
+    const LargeState* s = J.st + p;
+    if (s->status & CFSIM_INVALID_INPUT) return;
+    const FinalBufs<T> fb = final_bufs<T>(J, p, s);
+    const MarginArea<T> a = margin_area<T>(J, p, s, fb.nR, fb.nC);
+    if (!a.spread) return;
+    const double m = dev::wave_fmin((int)threadIdx.x < blocks ? a.part[threadIdx.x] : __builtin_inf());
+    if (threadIdx.x == 0) {
+        J.res[p].margin = m;
+        if (m <= J.tie_tol) J.res[p].status |= CFSIM_NEAR_TIE;
     }
-    while (q < n) {
-        const int h = free_in_step<32>(line, q, n, state, y);
-        if (h >= 0) return q + h;
-        q += 32;
-    }
-    y = -1;
-    return n;
 }
 
 // One workgroup per pair: greedy matching on the sorted lines, margin, outputs
@@ -1116,8 +1222,7 @@ __global__ __launch_bounds__(kFinishThreads) void large_finish(LargeJob J) {
     const bool rz = s->rz != 0;
     const FinalBufs<T> fb = final_bufs<T>(J, p, s);
     const int nR = fb.nR, nC = fb.nC;
-    const long long total = (long long)nR * nC;
-    T* S = fb.S;
+    const T* S = fb.S;
     const uint16_t* rl = fb.lists;                       // row r's columns in greedy order
     const uint16_t* cl = fb.lists + (long long)nR * nC;  // column c's rows in greedy order
 
@@ -1126,7 +1231,11 @@ __global__ __launch_bounds__(kFinishThreads) void large_finish(LargeJob J) {
     // entry always is).  A line's best free partner is the first free one in
     // its sorted order; partners are only ever taken, so each line keeps a
     // pointer into its order that only moves forward, and its current best in
-    // LDS: only a line whose best was taken reads its order again.
+    // LDS: only a line whose best was taken reads its order again.  Lines agree
+    // on what is best: a round of a 1000 x 2048 pair matches 6 and sends 740
+    // rows along their orders, the longest run 94 entries in the median round,
+    // so the rounds are bound by those runs (3.7 ms for 8 pairs of 512-2048
+    // nodes, 4.0 with the reads one entry and one line after the other).
     int* rstate = reinterpret_cast<int*>(smem);
     int* cstate = rstate + nR;
     uint16_t* rptr = reinterpret_cast<uint16_t*>(cstate + nC);
@@ -1149,23 +1258,24 @@ __global__ __launch_bounds__(kFinishThreads) void large_finish(LargeJob J) {
     int done = 0;
     bool first = true;
     while (done < need) {
-        for (int r = tid; r < nR; r += kFinishThreads) {
-            if (rstate[r] != -1) continue;
-            const int b = rbest[r];
-            if (!first && (b < 0 || cstate[b] == -1)) continue;   // still the best free partner (or none left)
-            int y;
-            const int q = first_free(rl + (long long)r * nC, rptr[r], nC, cstate, y);
-            rptr[r] = (uint16_t)q;
-            rbest[r] = (int16_t)y;
-        }
-        for (int c = tid; c < nC; c += kFinishThreads) {
-            if (cstate[c] != -1) continue;
-            const int b = cbest[c];
-            if (!first && (b < 0 || rstate[b] == -1)) continue;
-            int y;
-            const int q = first_free(cl + (long long)c * nR, cptr[c], nR, rstate, y);
-            cptr[c] = (uint16_t)q;
-            cbest[c] = (int16_t)y;
+        // two rows and two columns of a thread at a time
+        for (int b = tid; b < max(nR, nC); b += 2 * kFinishThreads) {
+            LineSearch rs[2], cs[2];
+#pragma unroll
+            for (int z = 0; z < 2; ++z) {
+                const int x = b + z * kFinishThreads;
+                rs[z].on = cs[z].on = false;
+                if (x < nR && rstate[x] == -1 && (first || (rbest[x] >= 0 && cstate[rbest[x]] != -1)))
+                    rs[z].begin(rl + (long long)x * nC, rptr[x], nC);
+                if (x < nC && cstate[x] == -1 && (first || (cbest[x] >= 0 && rstate[cbest[x]] != -1)))
+                    cs[z].begin(cl + (long long)x * nR, cptr[x], nR);
+            }
+#pragma unroll
+            for (int z = 0; z < 2; ++z) {
+                const int x = b + z * kFinishThreads;
+                rs[z].end(cstate, rptr + x, rbest + x);
+                cs[z].end(rstate, cptr + x, cbest + x);
+            }
         }
         first = false;
         __syncthreads();
@@ -1186,7 +1296,19 @@ __global__ __launch_bounds__(kFinishThreads) void large_finish(LargeJob J) {
     // relative margin of the matching; the picks go to a free slot (a 1 x 1
     // pair, whose slot holds one element, has no rival anyway)
     double margin = __builtin_inf();
-    if ((long long)nR + nC <= J.slot_elems) {
+    const MarginArea<T> ma = margin_area<T>(J, p, s, nR, nC);
+    if (ma.spread) {
+        for (int r = tid; r < nR; r += kFinishThreads) {
+            const int c = rstate[r];
+            ma.partner[r] = c;
+            ma.pv[r] = c >= 0 ? S[(long long)r * nC + c] : T(0);
+        }
+        for (int c = tid; c < nC; c += kFinishThreads) {
+            const int r = cstate[c];
+            ma.partner[nR + c] = r;
+            ma.pv[nR + c] = r >= 0 ? S[(long long)r * nC + c] : T(0);
+        }
+    } else if ((long long)nR + nC <= J.slot_elems) {
         T* pv = rz ? buf_of<T>(J, p, kSlotV) : buf_of<T>(J, p, (f + 3) & 3);
         margin = dev::greedy_margin<T, kFinishThreads>(S, nR, nC, false, rstate, cstate, pv, pv + nR, red);
         __syncthreads();  // red is reused by the score's sum
@@ -1198,10 +1320,6 @@ __global__ __launch_bounds__(kFinishThreads) void large_finish(LargeJob J) {
         const int jj = rstate[i];
         if (jj >= 0) sc += (double)S[(long long)i * nC + jj];
         if (J.match) J.match[mo + i] = jj;
-    }
-    if (J.S_out) {
-        T* So = reinterpret_cast<T*>(J.S_out) + (J.S_off ? J.S_off[p] : 0);
-        for (long long o = tid; o < total; o += kFinishThreads) So[o] = S[o];
     }
     const double score = dev::block_sum<NW>(sc, red);
     if (tid == 0) {
@@ -1270,6 +1388,12 @@ static int launch_finish(const LargeJob& J, hipStream_t stream) {
     if ((e = (int)hipGetLastError()) != 0) return e;
     hipLaunchKernelGGL(large_finish<T>, dim3(J.n_pairs), dim3(kFinishThreads), large_finish_lds(J.max_nodes), stream,
                        J);
+    if ((e = (int)hipGetLastError()) != 0) return e;
+    if ((long long)J.max_nodes * J.max_nodes < kMarginSpread) return 0;
+    const int per = 4096 / J.n_pairs, blocks = per < 1 ? 1 : (per < kMarginBlocks ? per : kMarginBlocks);
+    hipLaunchKernelGGL(large_margin<T>, dim3(blocks, J.n_pairs), dim3(kMarginThreads), 0, stream, J);
+    if ((e = (int)hipGetLastError()) != 0) return e;
+    hipLaunchKernelGGL(large_margin_done<T>, dim3(J.n_pairs), dim3(kWave), 0, stream, J, blocks);
     return (int)hipGetLastError();
 }
 

@@ -750,33 +750,15 @@ __device__ inline double block_min(double x, double* red) {
     return t;
 }
 
-// Relative margin of a finished greedy matching on S (nR x nC, row stride
-// nC; `swp`: S is stored transposed, so the order key of (r, c) is
-// c * nR + r).  A rival of the pick (r, c) is an entry of row r or column c
-// whose other line was still free when (r, c) was taken, that is, its other
-// line is unmatched or matched by a pick later in the greedy order.  The
-// margin is the smallest 1 - q / v over picks v and their rivals q (+inf if
-// there is none); a pick below the smallest normal number of T counts 0 (its
-// relative precision is gone).  Every thread of the workgroup must call it
-// after the matching's last barrier; pv_r[nR] and pv_c[nC] are scratch
-// (free memory the caller owns); one barrier before the reduction.
-template <typename T, int NT>
-__device__ inline double greedy_margin(const T* S, int nR, int nC, bool swp, const int* rstate, const int* cstate,
-                                       T* pv_r, T* pv_c, double* red) {
-    constexpr int NW = NT / kWave;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uni(tid / kWave);
-    for (int r = tid; r < nR; r += NT) {
-        const int c = rstate[r];
-        pv_r[r] = c >= 0 ? S[(long long)r * nC + c] : T(0);
-    }
-    for (int c = tid; c < nC; c += NT) {
-        const int r = cstate[c];
-        pv_c[c] = r >= 0 ? S[(long long)r * nC + c] : T(0);
-    }
-    __syncthreads();
+// The rivals of rows row0, row0 + step, ... (one wave; see greedy_margin):
+// this lane's smallest 1 - q / v.  pv_r and pv_c hold every line's pick.
+template <typename T>
+__device__ inline double margin_rows(const T* S, int nR, int nC, bool swp, const int* rstate, const int* cstate,
+                                     const T* pv_r, const T* pv_c, int row0, int step) {
+    const int lane = (int)(threadIdx.x & (kWave - 1));
     const T tiny = sizeof(T) == 8 ? T(DBL_MIN) : T(FLT_MIN);
     double m = __builtin_inf();
-    for (int r = wave; r < nR; r += NW) {
+    for (int r = row0; r < nR; r += step) {
         const int pr = uni(rstate[r]);
         const T va = pv_r[r];
         const Rank<T> ra = pr >= 0 ? Rank<T>::make(va, (uint32_t)(swp ? pr * nR + r : r * nC + pr)) : Rank<T>::none();
@@ -798,7 +780,34 @@ __device__ inline double greedy_margin(const T* S, int nR, int nC, bool swp, con
             }
         }
     }
-    return block_min<NW>(m, red);
+    return m;
+}
+
+// Relative margin of a finished greedy matching on S (nR x nC, row stride
+// nC; `swp`: S is stored transposed, so the order key of (r, c) is
+// c * nR + r).  A rival of the pick (r, c) is an entry of row r or column c
+// whose other line was still free when (r, c) was taken, that is, its other
+// line is unmatched or matched by a pick later in the greedy order.  The
+// margin is the smallest 1 - q / v over picks v and their rivals q (+inf if
+// there is none); a pick below the smallest normal number of T counts 0 (its
+// relative precision is gone).  Every thread of the workgroup must call it
+// after the matching's last barrier; pv_r[nR] and pv_c[nC] are scratch
+// (free memory the caller owns); one barrier before the reduction.
+template <typename T, int NT>
+__device__ inline double greedy_margin(const T* S, int nR, int nC, bool swp, const int* rstate, const int* cstate,
+                                       T* pv_r, T* pv_c, double* red) {
+    constexpr int NW = NT / kWave;
+    const int tid = threadIdx.x, wave = uni(tid / kWave);
+    for (int r = tid; r < nR; r += NT) {
+        const int c = rstate[r];
+        pv_r[r] = c >= 0 ? S[(long long)r * nC + c] : T(0);
+    }
+    for (int c = tid; c < nC; c += NT) {
+        const int r = cstate[c];
+        pv_c[c] = r >= 0 ? S[(long long)r * nC + c] : T(0);
+    }
+    __syncthreads();
+    return block_min<NW>(margin_rows<T>(S, nR, nC, swp, rstate, cstate, pv_r, pv_c, wave, NW), red);
 }
 
 }  // namespace dev
