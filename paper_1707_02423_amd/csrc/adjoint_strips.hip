@@ -45,7 +45,7 @@ constexpr int kListEdges = kBwdLds / 12;  // edges of a pair that fits the other
 constexpr int kEdgeGroups = kEdgeWaves;   // workgroups of a pair's edge sums
 
 struct AdjPair {
-    int p, nR, nC, K, s_last, kept_a, kept_b, strips, active, any_long;
+    int p, nR, nC, K, s_last, kept_a, kept_b, strips, active;
 };
 // A partial sum of a pair's edges (a workgroup's work) or a strip (a wave's),
 // with its pair (one read instead of two dependent ones).
@@ -164,11 +164,6 @@ __global__ __launch_bounds__(kNT) void adj_init(AdjJob A) {
         st.active = !((fr->status & CFSIM_DEGENERATE) || fr->iters == 0 || gs == 0.0);
     }
     if (blockIdx.x == 0) {
-        int lng = 0;
-        if (st.active)
-            for (int i = threadIdx.x; i < b.n; i += kNT)
-                lng |= b.rp[i + 1] - b.rp[i] > 2 || b.cp[i + 1] - b.cp[i] > kDP;
-        lng = __syncthreads_or(lng);
         if (threadIdx.x == 0) {
             st.p = p;
             if (st.active) {
@@ -179,7 +174,6 @@ __global__ __launch_bounds__(kNT) void adj_init(AdjJob A) {
                 st.kept_a = a.rp[a.n];
                 st.kept_b = b.rp[b.n];
                 st.strips = (a.n + kRows - 1) / kRows;
-                st.any_long = lng;
             }
             A.pairs[slot] = st;
         }
@@ -373,14 +367,14 @@ __device__ __forceinline__ void stage(Load& ld, const Scales& scales, int nR, co
 // long_row_terms for column i from its slots: two orders, by the length of the
 // column's lists; entries of longer lists come from its graph.
 template <typename T, typename Load>
-__device__ __forceinline__ T row_rest(const Load& ld, const ColSlots<T, kDP>& k, int nR, int pad, int i, bool rest,
+__device__ __forceinline__ T row_rest(const Load& ld, const ColSlots<T, kDP>& k, int nR, int pad, int i,
                                       const GraphRef& R, const GraphRef& C, int c) {
     const auto X = [&](int row, int off) {  // neighbour at byte offset `off` of P1 / P2
         const uint32_t u = (uint32_t)min(off / (int)(kRows * sizeof(T)), nR - 1);
         return ld.finish(ld.read(((uint32_t)row * (uint32_t)nR + u) * (uint32_t)sizeof(T)));
     };
     const int cs0 = C.rp[c] + 2, cs1 = C.rp[c + 1], cp0 = C.cp[c] + kDP, cp1 = C.cp[c + 1];
-    const bool longer = rest && i < nR && (R.rp[i + 1] - R.rp[i] > 2 || R.cp[i + 1] - R.cp[i] > kDP);
+    const bool longer = k.lng;
     const bool inner = !longer && k.po[3] == pad;   // at most 2 successors and 3 predecessors
     T y = T(0);
     if (inner) {
@@ -446,7 +440,6 @@ __device__ __forceinline__ void strip_apply(const AdjItem& item, const Slot<T>& 
     const StripTab<T>* tab = S.tabs() + item.index;
     const Cols<T> cols = S.cols(nR);
     const int flags = uni(tab->long_rows);
-    const bool rest = item.st.any_long != 0;
     const auto graph_b = [&] { return graph_of(J.set, J.pair_b[item.st.p]); };
     if (lane < 2) (lane ? P2 : P1)[col_stride(nR)] = Quad<T>{};
     stage(ld, [&] { scales(ld); }, nR, tab, P1, P2);
@@ -461,7 +454,8 @@ __device__ __forceinline__ void strip_apply(const AdjItem& item, const Slot<T>& 
 #pragma unroll
             for (int r = 0; r < kRows; ++r) m[r] = at_byte(mul, o + (r < left ? r : 0) * rowb);
         }
-        const Quad<T> y = gather_slots<T, kDP>(load_col<T, kDP>(cols, i), i, P1, P2, rest, graph_b);
+        const ColSlots<T, kDP> k = load_col<T, kDP>(cols, i);
+        const Quad<T> y = gather_slots<T, kDP>(k, i, P1, P2, __ballot(k.lng) != 0, graph_b);
         if (i >= nR) continue;
         put_quad(out_n + (i * ldn + c0), y);  // past n_C: the row's padding
 #pragma unroll
@@ -480,7 +474,7 @@ __device__ __forceinline__ void strip_apply(const AdjItem& item, const Slot<T>& 
             for (int r = 0; r < kRows; ++r) {
                 if (!((flags >> r) & 1) || i >= nR) continue;
                 const int o = (c0 + r) * nR + i;
-                const T v = out_x[o] + row_rest<T, Load>(ld, k, nR, pad, i, rest, R, C, c0 + r);
+                const T v = out_x[o] + row_rest<T, Load>(ld, k, nR, pad, i, R, C, c0 + r);
                 out_x[o] = v;
                 out_n[i * ldn + c0 + r] = v;
                 sum += (double)v * (double)(mul ? T(mul[o] * mul_inv) : v);

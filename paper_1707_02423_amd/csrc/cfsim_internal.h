@@ -394,6 +394,7 @@ struct LargeState {
     int final_step;      // k of the returned iterate
     double nu, delta;    // reported norm and last even-step change
     double nu_k[4];      // nu_k of the iterate held in buffer k % 4 (1 for S_0)
+    double inv_k[4];     // 1 / nu_k
 };
 
 struct LargeJob {

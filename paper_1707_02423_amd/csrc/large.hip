@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256) void large_init(LargeJob J) {
         s->final_step = 0;
         s->nu = 0.0;
         s->delta = __builtin_inf();
-        for (int b = 0; b < 4; ++b) s->nu_k[b] = 1.0;
+        for (int b = 0; b < 4; ++b) s->nu_k[b] = s->inv_k[b] = 1.0;
     }
     if (!ok) return;
     const bool swap = rz && nB < nA;
@@ -262,6 +262,7 @@ __global__ __launch_bounds__(kStepThreads) void large_reduce(LargeJob J, int k) 
             if (!stop && compute) {
                 const double nu = sqrt(nu2s);
                 s->nu_k[k & 3] = nu;
+                s->inv_k[k & 3] = 1.0 / nu;
                 if (k == J.max_iter && (k & 1)) {  // odd max_iter: no change test at k
                     s->final_step = k;
                     s->nu = nu;
@@ -655,9 +656,9 @@ void large_strip(LargeJob J, int k) {
         const T* src = buf_of<T>(J, p, (k - 1) & 3);
         T* dst = buf_of<T>(J, p, k & 3);
         const T* old = buf_of<T>(J, p, (k - 3) & 3);
-        const T c0v = T(1.0 / sqrt((double)s->nA * (double)s->nB));
-        const T sig = T(1.0 / s->nu_k[(k - 1) & 3]);   // sigma_{k-1} (1 for S_0)
-        const T sig3 = T(1.0 / s->nu_k[(k - 3) & 3]);  // sigma_{k-3}
+        const T c0v = k == 1 || k == 3 ? T(1.0 / sqrt((double)s->nA * (double)s->nB)) : T(0);
+        const T sig = T(s->inv_k[(k - 1) & 3]);   // sigma_{k-1} (1 for S_0)
+        const T sig3 = T(s->inv_k[(k - 3) & 3]);  // sigma_{k-3}
         GraphRef A, B;
         pair_graphs(J, p, &A, &B);
         unsigned char* base = strip_base<T>(J, p);
@@ -667,7 +668,8 @@ void large_strip(LargeJob J, int k) {
         double nu2 = 0.0, d2 = 0.0;
         if (compute && k > 1) {
             __syncthreads();  // the strip before has been gathered
-            stage_sources<NW>(src, nR, tab, P1, P2);
+            if (threadIdx.x < 2) (threadIdx.x ? P2 : P1)[col_stride(nR)] = Quad<T>{};
+            wave_sources(src, nR, tab, P1, P2, wave, NW);
             __syncthreads();
         }
         const Cols<T> cols = carve_cols<T>(base, nR, kStripDP);
@@ -676,9 +678,9 @@ void large_strip(LargeJob J, int k) {
             const int i = ch * kWave + lane;
             const bool valid = i < nR;
             if (compute && k > 1) {
-                Quad<T> y = gather_col<T, kStripDP>(cols, i, P1, P2, false, B);
-                const bool lng = valid && (B.rp[i + 1] - B.rp[i] > kLS || B.cp[i + 1] - B.cp[i] > kLP);
-                if (__ballot(lng) != 0 && lng) {
+                const ColSlots<T, kStripDP> slots = load_col<T, kStripDP>(cols, i);
+                Quad<T> y = gather_slots<T, kStripDP>(slots, i, P1, P2, false, [&] { return B; });
+                if (slots.lng) {
                     const Quad<T> rest = col_lists_rest<T>(B, i, P1, P2);
 #pragma unroll
                     for (int r = 0; r < kRows; ++r) y.v[r] += rest.v[r];

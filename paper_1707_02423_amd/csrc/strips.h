@@ -27,7 +27,6 @@ constexpr int kThreads = 512;      // workgroup of a strip
 constexpr int kWaves = kThreads / kWave;
 constexpr int kSrcS = 8;           // merged successor sources of a strip (4 rows, at most 2 each)
 constexpr int kSrcP = 16;          // merged predecessor sources (4 rows, at most 4 each)
-constexpr int kSrcFast = 8;        // predecessor sources whose reads are issued together
 
 // Sources of one strip: byte offsets of rows of X and the four rows' weights
 // of each.
@@ -43,7 +42,8 @@ struct alignas(16) StripTab {
 
 // Lists of the columns (R nodes), one array per slot of `stride` entries:
 // byte offsets of the neighbours in P1 / P2 and weights; absent slots point at
-// the zero entry behind the last column, with weight 0.
+// the zero entry behind the last column, with weight 0.  Bit 0 of the first
+// successor's offset: the column's lists are longer than the slots.
 template <typename T>
 struct Cols {
     const int* so;   // [2][stride]
@@ -83,7 +83,8 @@ __device__ inline void build_col(const GraphRef& R, int i, Cols<T> c) {
     constexpr int vb = kRows * (int)sizeof(T);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        const_cast<int*>(c.so)[q * c.stride + i] = (q < ns ? R.ci[sb + q] : c.stride) * vb;
+        const_cast<int*>(c.so)[q * c.stride + i] =
+            (q < ns ? R.ci[sb + q] : c.stride) * vb + (q == 0 && (ns > 2 || np > DP) ? 1 : 0);
         const_cast<T*>(c.sw)[q * c.stride + i] = q < ns ? T(R.w[sb + q]) : T(0);
     }
 #pragma unroll
@@ -171,67 +172,10 @@ struct Quad {
 };
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// acc[r] += w[r] * x for the strip's four rows (lane: one column of x).
-// FP32: one outer product per 64 columns, the weight of row (lane & 3) in wl.
-__device__ __forceinline__ void add_source(Quad<float>& acc, float wl, const float*, float x) {
-    floatx4 a = {acc.v[0], acc.v[1], acc.v[2], acc.v[3]};
-    a = __builtin_amdgcn_mfma_f32_4x4x1f32(wl, x, a, 0, 0, 0);
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) acc.v[r] = a[r];
-}
-__device__ __forceinline__ void add_source(Quad<double>& acc, double, const double* w, double x) {
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) acc.v[r] = dev::fma_t(w[r], x, acc.v[r]);
-}
-
-// Stage A: P1 and P2 of the strip (X: row stride nR) into LDS.  The whole
-// wave takes part in every source (the matrix instruction reads all lanes):
-// lanes past the last column read the last one.
-template <int NW, typename T>
-__device__ __forceinline__ void stage_sources(const T* X, int nR, const StripTab<T>* t, Quad<T>* P1, Quad<T>* P2) {
-    const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int wave = dev::uni((int)threadIdx.x / kWave);
-    const int nch = (nR + kWave - 1) / kWave;
-    T ws[kSrcS], wp[kSrcFast];
-    int ss[kSrcS], sp[kSrcFast];
-#pragma unroll
-    for (int q = 0; q < kSrcS; ++q) {
-        ws[q] = t->ws[q][lane & (kRows - 1)];
-        ss[q] = dev::uni(t->src_s[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < kSrcFast; ++q) {
-        wp[q] = t->wp[q][lane & (kRows - 1)];
-        sp[q] = dev::uni(t->src_p[q]);
-    }
-    const int np = dev::uni(t->np);
-    if (threadIdx.x == 0) {
-        P1[col_stride(nR)] = Quad<T>{};
-        P2[col_stride(nR)] = Quad<T>{};
-    }
-    for (int ch = wave; ch < nch; ch += NW) {
-        const int col = ch * kWave + lane, at = min(col, nR - 1);
-        T xs[kSrcS], xp[kSrcFast];
-#pragma unroll
-        for (int q = 0; q < kSrcS; ++q) xs[q] = at_byte(X, (uint32_t)ss[q] + (uint32_t)at * (uint32_t)sizeof(T));
-#pragma unroll
-        for (int q = 0; q < kSrcFast; ++q) xp[q] = at_byte(X, (uint32_t)sp[q] + (uint32_t)at * (uint32_t)sizeof(T));
-        Quad<T> a{}, b{};
-#pragma unroll
-        for (int q = 0; q < kSrcS; ++q) add_source(a, ws[q], t->ws[q], xs[q]);
-#pragma unroll
-        for (int q = 0; q < kSrcFast; ++q) add_source(b, wp[q], t->wp[q], xp[q]);
-        for (int q = kSrcFast; q < np; ++q)
-            add_source(b, t->wp[q][lane & (kRows - 1)], t->wp[q],
-                       at_byte(X, (uint32_t)dev::uni(t->src_p[q]) + (uint32_t)at * (uint32_t)sizeof(T)));
-        P1[col] = a;
-        P2[col] = b;
-    }
-}
-
-// Stage A by one wave, all chunks, into its own P1 and P2 (strips of
-// workgroups that stay with their pair).  FP32: one register holds the weights
-// of 16 sources (lane 4 q + r), of which the matrix instruction broadcasts the
+// Stage A by one wave: P1 and P2 of the strip (X: row stride nR) for the chunks
+// of 64 columns ch0, ch0 + step, ....  The whole wave takes part in every source
+// (the matrix instruction reads all lanes): lanes past the last column read the
+// last one.  FP32: one register holds the weights of 16 sources (lane 4 q + r), of which the matrix instruction broadcasts the
 // block it needs (cbsz = 4, abid = the source).
 template <int Q>
 __device__ __forceinline__ void add_block(floatx4& acc, float w, float x) {
@@ -245,14 +189,14 @@ __device__ __forceinline__ void add_blocks(floatx4& acc, float w, const float (&
     add_block<W + 3>(acc, w, x[3]);
 }
 __device__ __forceinline__ void wave_sources(const float* X, int nR, const StripTab<float>* t, Quad<float>* P1,
-                                             Quad<float>* P2) {
+                                             Quad<float>* P2, int ch0 = 0, int step = 1) {
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const float* wt = &t->ws[0][0];  // ws and wp lie one behind the other
     const float w = wt[lane], w2 = wt[64 + (lane & 31)];
     const int src = t->src_s[lane < 24 ? lane : 0];  // src_s and src_p too
     const int ns = dev::uni(t->ns), np = dev::uni(t->np);
     const int nch = (nR + kWave - 1) / kWave;
-    for (int ch = 0; ch < nch; ++ch) {
+    for (int ch = ch0; ch < nch; ch += step) {
         const int col = ch * kWave + lane;
         const uint32_t at = (uint32_t)min(col, nR - 1) * 4u;
         float x[6][4];
@@ -282,12 +226,12 @@ __device__ __forceinline__ void wave_sources(const float* X, int nR, const Strip
     }
 }
 __device__ __forceinline__ void wave_sources(const double* X, int nR, const StripTab<double>* t, Quad<double>* P1,
-                                             Quad<double>* P2) {
+                                             Quad<double>* P2, int ch0 = 0, int step = 1) {
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const int src = t->src_s[lane < 24 ? lane : 0];  // src_s and src_p lie one behind the other
     const int ns = dev::uni(t->ns), np = dev::uni(t->np);
     const int nch = (nR + kWave - 1) / kWave;
-    for (int ch = 0; ch < nch; ++ch) {
+    for (int ch = ch0; ch < nch; ch += step) {
         const int col = ch * kWave + lane;
         const uint32_t at = (uint32_t)min(col, nR - 1) * 8u;
         double x[4][4];
@@ -376,6 +320,7 @@ template <typename T, int DP>
 struct ColSlots {
     int so[2], po[DP];
     T sw[2], pw[DP];
+    bool lng;   // longer lists
 };
 template <typename T, int DP>
 __device__ __forceinline__ ColSlots<T, DP> load_col(const Cols<T>& c, int i) {
@@ -385,6 +330,8 @@ __device__ __forceinline__ ColSlots<T, DP> load_col(const Cols<T>& c, int i) {
         k.so[q] = c.so[q * c.stride + i];
         k.sw[q] = c.sw[q * c.stride + i];
     }
+    k.lng = (k.so[0] & 1) != 0;
+    k.so[0] &= ~1;
 #pragma unroll
     for (int q = 0; q < DP; ++q) {
         k.po[q] = c.po[q * c.stride + i];

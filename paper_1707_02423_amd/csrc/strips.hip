@@ -109,17 +109,21 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
     const StripTab<T>* tab = reinterpret_cast<const StripTab<T>*>(S.tabs) + strip;
     Quad<T>* P1 = reinterpret_cast<Quad<T>*>(smem);
     Quad<T>* P2 = P1 + col_stride(nR) + 1;
-    stage_sources<kWaves>(Xc, nR, tab, P1, P2);
+    // what does not depend on the staged rows is read before them
+    const Cols<T> cols = carve_cols<T>(S.cols, nR, kDP);
+    const int nch = (nR + kWave - 1) / kWave;
+    ColSlots<T, kDP> slots{};
+    if (wave < nch) slots = load_col<T, kDP>(cols, wave * kWave + lane);
+    if (threadIdx.x < 2) (threadIdx.x ? P2 : P1)[col_stride(nR)] = Quad<T>{};
+    wave_sources(Xc, nR, tab, P1, P2, wave, kWaves);
     const StripState st = state_after(S, k - 1);
     if (strip == 0 && threadIdx.x == 0) S.st[(k - 1) & 1] = st;
     if (st.status != 0) return;  // the same in every thread
     const T sigma = k == 1 ? T(1) : T(st.inv);
-    const Cols<T> cols = carve_cols<T>(S.cols, nR, kDP);
     const GraphRef R = pick_graph(S.swap != 0, S.J.ga, S.J.gb), C = pick_graph(S.swap != 0, S.J.gb, S.J.ga);
     const int long_rows = uni(tab->long_rows);
     __syncthreads();
     double v[3] = {0.0, 0.0, 0.0};
-    const int nch = (nR + kWave - 1) / kWave;
     for (int ch = wave; ch < nch; ch += kWaves) {
         const int i = ch * kWave + lane;
         const bool valid = i < nR;
@@ -127,8 +131,8 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
 #pragma unroll
         for (int r = 0; r < kRows; ++r)
             old[r] = even && valid && c0 + r < nC ? Xn[(long long)(c0 + r) * nR + i] : T(0);
-        const bool lng = valid && (R.rp[i + 1] - R.rp[i] > 2 || R.cp[i + 1] - R.cp[i] > kDP);
-        Quad<T> y = gather_col<T, kDP>(cols, i, P1, P2, __ballot(lng) != 0, R);
+        if (ch != wave) slots = load_col<T, kDP>(cols, i);
+        const Quad<T> y = gather_slots<T, kDP>(slots, i, P1, P2, __ballot(slots.lng) != 0, [&] { return R; });
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
             if (!valid || c0 + r >= nC || ((long_rows >> r) & 1)) continue;
