@@ -613,7 +613,7 @@ size_t cfsim_score_workspace_size(const cfsim_context* ctx, int32_t n_a, int32_t
     if (opt->resize == CFSIM_RESIZE_BILINEAR) return large_ws_bytes(1, n_a > n_b ? n_a : n_b, (int)esize, 6);
     const size_t least = score_ws_min(n_a, n_b, opt);
     if (least < ((size_t)64 << 10)) return least;  // always in LDS
-    // the strip path's lists and tables beside them
+    // the strip path's buffers, lists and tables
     const size_t strips = align256(cfsim::strip_bytes(n_a, n_b, (int)esize));
     return least > strips ? least : strips;
 }
@@ -710,9 +710,9 @@ cfsim_status cfsim_score(cfsim_context* ctx, const cfsim_graph* A, const cfsim_g
     if (e != 0) return hip_fail(e, "hipSetDevice");
     hipStream_t st = static_cast<hipStream_t>(stream);
     // A pair past LDS runs on strips (one launch per update over the whole
-    // chip) when the workspace holds their tables, as the workspace that
-    // cfsim_score_workspace_size names does; with less (the static scratch of
-    // cfsim_score_noalloc near its limit) in one workgroup.
+    // chip) when the workspace holds their buffers and tables, as the workspace
+    // that cfsim_score_workspace_size names does; with less (down to the two
+    // buffers of the global kernel) in one workgroup.
     const int largest = A->n > B->n ? A->n : B->n;
     if (variant == cfsim::kBucketGlobal && largest <= cfsim::kStripMaxNodes && opt->max_iter <= cfsim::kStripMaxIter &&
         ws_bytes >= cfsim::strip_bytes(A->n, B->n, esize)) {

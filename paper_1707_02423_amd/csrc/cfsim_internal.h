@@ -468,6 +468,8 @@ bool large_on_strips(int max_nodes, int esize);      // whether a strip's rows f
 int large_step_grid(int num_cus);
 int set_large_attributes();
 int launch_large(int dtype, const LargeJob& job, int grid, hipStream_t stream);
+// Its kernels after the last update: S, matching, margin and results.
+int launch_large_finish(int dtype, const LargeJob& job, hipStream_t stream);
 
 // Adjoint (adjoint.hip).
 long long backward_slot_bytes(int max_iter, int ckpt, long long slot_elems, int esize);

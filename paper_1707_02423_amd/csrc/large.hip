@@ -1470,6 +1470,10 @@ static int launch_large_t(const LargeJob& J, int grid, hipStream_t stream) {
     return launch_finish<T>(J, stream);
 }
 
+int launch_large_finish(int dtype, const LargeJob& J, hipStream_t stream) {
+    return dtype == CFSIM_F64 ? launch_finish<double>(J, stream) : launch_finish<float>(J, stream);
+}
+
 int launch_large(int dtype, const LargeJob& J, int grid, hipStream_t stream) {
     return dtype == CFSIM_F64 ? launch_large_t<double>(J, grid, stream) : launch_large_t<float>(J, grid, stream);
 }

@@ -29,7 +29,6 @@
 
 #include "cfsim_internal.h"
 #include "pair_device.h"
-#include "strip_job.h"
 #include "strips.h"
 
 namespace cfsim {
@@ -2037,25 +2036,6 @@ void damped_global_kernel(PairJob J) {
     __shared__ double red[4 * (kGlobalThreads / kWave)];
     __shared__ int s_item, s_count[2];
     drive<true, T, kGlobalThreads, 1, kModeDamped>(J, smem, red, &s_item, s_count, nullptr);
-}
-
-// Matching and outputs of the plain pair that ran on strips (strips.hip): S
-// stands in the buffer the last step did not write.
-template <typename T>
-__global__ __launch_bounds__(kGlobalThreads) __attribute__((amdgpu_waves_per_eu(4)))
-void strip_finish_kernel(StripJob S) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[4 * (kGlobalThreads / kWave)];
-    __shared__ int s_count[2];
-    const StripState st = *S.fin;
-    const PairShape sh = make_shape(S.J.ga.n, S.J.gb.n, S.swap, kGlobalThreads / kWave);
-    // the matching's cached bests take the room of the lists: all of the LDS
-    const int spare = (int)((kGlobalLds - lds_lists_bytes(sh.nR, sh.nC, 0, 0, sizeof(T)) - 64) / (4 * sizeof(Edge<T>)));
-    const Lists<T> G = carve_lists<T>(smem, sh.nR, sh.nC, spare, spare);
-    IterOut it{st.iters > 0 ? sqrt(st.tot) : 0.0, st.d2 >= 0.0 ? sqrt(st.d2) : __builtin_inf(), st.iters, st.status, 0};
-    T* Sx = reinterpret_cast<T*>((st.iters & 1) ? S.x0 : S.x1);
-    T* St = reinterpret_cast<T*>((st.iters & 1) ? S.x1 : S.x0);
-    match_and_write<T, kGlobalThreads, true>(S.J, 0, S.J.ga, S.J.gb, sh, Sx, St, G, it, S.J.res, red, s_count);
 }
 
 // The kernel of one measure and arithmetic type for a bucket (instantiations

@@ -20,20 +20,19 @@ struct StripJob {
     PairJob J;             // the pair (ga, gb), options and outputs
     int swap, nR, nC;      // orientation (as PairShape)
     int strips;
-    unsigned char *x0, *x1;  // X_k in x0 (k even) or x1, nC x nR
+    unsigned char* x[4];   // X_k in x[k % 4], nC x nR
+    long long slot_elems;  // elements from one buffer to the next
     unsigned char* cols;   // column lists (strips.h)
     unsigned char* tabs;   // strip tables
     double* part;          // norm partials: two areas of 3 * strips
     StripState* st;        // [2] states after alternate steps
-    StripState* fin;
+    LargeState* large;     // the final state for the kernels that match large pairs
 };
 
 size_t strip_bytes(int nA, int nB, int esize);
 // Fills the descriptor's shape and carves its arrays from ws (strip_bytes()).
 void carve_strips(StripJob* S, void* ws, int esize);
 int set_strip_attributes();
-const void* strip_finish_f32();
-const void* strip_finish_f64();
 int launch_strips(int dtype, const StripJob& job, hipStream_t stream);
 
 }  // namespace cfsim

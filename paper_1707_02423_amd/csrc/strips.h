@@ -392,15 +392,15 @@ __device__ __forceinline__ Quad<T> gather_col(const Cols<T>& c, int i, const Qua
 }
 
 // The rows of a strip whose lists are longer than the slots, by the pair
-// kernels' rules: all of the row, from P1 and P2, X_{k-1} (Xc) and the values
-// it overwrites (Xn).  Out of line and after the other rows, so that the loop
+// kernels' rules: all of the row, from P1 and P2, X_{k-1} (Xc) and X_{k-2}
+// (Xo).  Out of line and after the other rows, so that the loop
 // over the columns holds no call.  Columns of chunks ch0, ch0 + step, ...;
 // returns nu^2 and the even-step sums.
 struct RowSums {
     double nu2, dy2, dyy;
 };
 template <typename T, int DP>
-__device__ __noinline__ RowSums long_rows_pass(const T* Xc, T* Xn, int nR, int nC, int c0, int long_rows,
+__device__ __noinline__ RowSums long_rows_pass(const T* Xc, T* Xn, const T* Xo, int nR, int nC, int c0, int long_rows,
                                                unsigned char* cols_at, const Quad<T>* P1, const Quad<T>* P2,
                                                GraphRef R, GraphRef C, T sigma, int even, int ch0, int step) {
     RowSums s{0.0, 0.0, 0.0};
@@ -420,7 +420,7 @@ __device__ __noinline__ RowSums long_rows_pass(const T* Xc, T* Xn, int nR, int n
             const T f = (z + long_row_terms<T>(at_X, R, C, i, c0 + r)) * sigma;
             T* at = Xn + (long long)(c0 + r) * nR + i;
             if (even) {
-                const double dy = (double)f - (double)*at;
+                const double dy = (double)f - (double)Xo[(long long)(c0 + r) * nR + i];
                 s.dy2 += dy * dy;
                 s.dyy += dy * (double)f;
             }

@@ -6,8 +6,11 @@
 // reduction between.  The results are those of the one-workgroup kernel.
 //
 // Bound by the latency of one launch: its start, three dependent reads from
-// memory and the barrier between the two stages, 10.8 us per update for a
-// 333 x 410 FP32 pair (103 workgroups) against 170 us on one CU.
+// memory and the barrier between the two stages, 6.3 us per update for a
+// 333 x 410 FP32 pair (103 workgroups) against 170 us on one CU.  Such a pair is
+// matched in 0.6 ms by the large path's kernels (lines sorted over the chip), in
+// 1.9 ms by one workgroup that keeps the columns' bests (which most columns
+// agree on, so that most of them are looked up again at every pick).
 #include "strip_job.h"
 #include "strips.h"
 
@@ -31,7 +34,7 @@ __global__ __launch_bounds__(256) void strip_build(StripJob S) {
     StripTab<T>* tabs = reinterpret_cast<StripTab<T>*>(S.tabs);
     for (int s = tid; s < S.strips; s += nt) build_strip<T, kDP>(C, s * kRows, S.nR, tabs + s);
     const T s0 = T(1.0 / sqrt((double)S.nR * (double)S.nC));
-    T* X = reinterpret_cast<T*>(S.x0);
+    T* X = reinterpret_cast<T*>(S.x[0]);
     for (long long t = tid; t < (long long)S.nR * S.nC; t += nt) X[t] = s0;
     if (blockIdx.x != 0) return;
     if (threadIdx.x < 2) pos[threadIdx.x] = 0;
@@ -104,8 +107,9 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
     if (strip >= S.strips * (xcd + 1) / 8) return;
     const int c0 = strip * kRows;
     const int nR = S.nR, nC = S.nC;
-    const T* Xc = reinterpret_cast<const T*>(((k - 1) & 1) ? S.x1 : S.x0);
-    T* Xn = reinterpret_cast<T*>((k & 1) ? S.x1 : S.x0);
+    const T* Xc = reinterpret_cast<const T*>(S.x[(k - 1) & 3]);
+    T* Xn = reinterpret_cast<T*>(S.x[k & 3]);
+    const T* Xo = reinterpret_cast<const T*>(S.x[(k - 2) & 3]);  // X_{k-2}
     const StripTab<T>* tab = reinterpret_cast<const StripTab<T>*>(S.tabs) + strip;
     Quad<T>* P1 = reinterpret_cast<Quad<T>*>(smem);
     Quad<T>* P2 = P1 + col_stride(nR) + 1;
@@ -130,7 +134,7 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
         T old[kRows];
 #pragma unroll
         for (int r = 0; r < kRows; ++r)
-            old[r] = even && valid && c0 + r < nC ? Xn[(long long)(c0 + r) * nR + i] : T(0);
+            old[r] = even && valid && c0 + r < nC ? Xo[(long long)(c0 + r) * nR + i] : T(0);
         if (ch != wave) slots = load_col<T, kDP>(cols, i);
         const Quad<T> y = gather_slots<T, kDP>(slots, i, P1, P2, __ballot(slots.lng) != 0, [&] { return R; });
 #pragma unroll
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
         }
     }
     if (long_rows) {
-        const RowSums ls = long_rows_pass<T, kDP>(Xc, Xn, nR, nC, c0, long_rows, S.cols, P1, P2, R, C, sigma, even, wave,
+        const RowSums ls = long_rows_pass<T, kDP>(Xc, Xn, Xo, nR, nC, c0, long_rows, S.cols, P1, P2, R, C, sigma, even, wave,
                                                   kWaves);
         v[0] += ls.nu2;
         v[1] += ls.dy2;
@@ -166,37 +170,28 @@ __global__ __launch_bounds__(kThreads) void strip_update(StripJob S, int k) {
     }
 }
 
-// S = sigma X^T of the last step, nR x nC, into the other buffer, in 32 x 32
-// tiles through LDS; the final state into fin.
-template <typename T>
-__global__ __launch_bounds__(256) void strip_final(StripJob S) {
-    __shared__ T tile[32][33];
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+// The final state as the large path keeps it.
+__global__ void strip_large_state(StripJob S) {
     const StripState st = state_after(S, S.J.max_iter);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *S.fin = st;
-    const T* X = reinterpret_cast<const T*>((st.iters & 1) ? S.x1 : S.x0);
-    T* D = reinterpret_cast<T*>((st.iters & 1) ? S.x0 : S.x1);
-    const T sigma = st.iters > 0 ? T(st.inv) : T(1);
-    const int ntc = (S.nC + 31) / 32, ntiles = ntc * ((S.nR + 31) / 32);
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const int i0 = (t / ntc) * 32, j0 = (t % ntc) * 32;
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int c = j0 + ty + 8 * s, i = i0 + tx;
-            if (c < S.nC && i < S.nR) tile[ty + 8 * s][tx] = X[(long long)c * S.nR + i] * sigma;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int i = i0 + ty + 8 * s, c = j0 + tx;
-            if (i < S.nR && c < S.nC) D[(long long)i * S.nC + c] = tile[tx][ty + 8 * s];
-        }
+    if (threadIdx.x != 0) return;
+    LargeState l{};
+    l.nA = S.J.ga.n;
+    l.nB = S.J.gb.n;
+    l.nR = l.nB;
+    l.nC = l.nA;
+    l.status = st.status;
+    l.final_step = st.iters;
+    l.nu = st.iters > 0 ? sqrt(st.tot) : 0.0;
+    l.delta = st.d2 >= 0.0 ? sqrt(st.d2) : __builtin_inf();
+    for (int b = 0; b < 4; ++b) {
+        l.nu_k[b] = st.iters > 0 ? l.nu : 1.0;
+        l.inv_k[b] = 1.0 / l.nu_k[b];
     }
+    *S.large = l;
 }
 
 template <typename T>
-int launch_t(const StripJob& S, const void* finish, hipStream_t stream) {
+int launch_t(const StripJob& S, hipStream_t stream) {
     hipLaunchKernelGGL(strip_build<T>, dim3(64), dim3(256), 0, stream, S);
     int e = (int)hipGetLastError();
     if (e != 0) return e;
@@ -205,11 +200,25 @@ int launch_t(const StripJob& S, const void* finish, hipStream_t stream) {
         hipLaunchKernelGGL(strip_update<T>, dim3(grid), dim3(kThreads), strip_lds<T>(S.nR), stream, S, k);
         if ((e = (int)hipGetLastError()) != 0) return e;
     }
-    hipLaunchKernelGGL(strip_final<T>, dim3(256), dim3(256), 0, stream, S);
+    hipLaunchKernelGGL(strip_large_state, dim3(1), dim3(kWave), 0, stream, S);
     if ((e = (int)hipGetLastError()) != 0) return e;
-    StripJob arg = S;
-    void* args[] = {&arg};
-    return (int)hipLaunchKernel(finish, dim3(1), dim3(kGlobalThreads), args, kGlobalLds, stream);
+    LargeJob L{};
+    L.single = 1;
+    L.ga = S.J.ga;
+    L.gb = S.J.gb;
+    L.n_pairs = 1;
+    L.max_nodes = S.nR > S.nC ? S.nR : S.nC;
+    L.max_iter = S.J.max_iter;
+    L.tie_tol = S.J.tie_tol;
+    L.res = S.J.res;
+    L.match = S.J.match;
+    L.S_out = S.J.S_out;
+    L.st = S.large;
+    L.bufs = S.x[0];
+    L.nslots = 4;
+    L.slot_elems = S.slot_elems;
+    L.strips = !S.swap;  // X is S^T, or with swap S itself
+    return launch_large_finish(sizeof(T) == 8 ? CFSIM_F64 : CFSIM_F32, L, stream);
 }
 
 template <typename T>
@@ -221,21 +230,22 @@ size_t carve_t(StripJob* S, unsigned char* ws, int nR, int nC) {
         o += align16(b);
         return p;
     };
-    unsigned char* x0 = take((size_t)nR * nC * sizeof(T));
-    unsigned char* x1 = take((size_t)nR * nC * sizeof(T));
+    const size_t buf = align16((size_t)nR * nC * sizeof(T));
+    unsigned char* x = take(4 * buf);
     unsigned char* cols = take(cols_bytes<T>(nR, kDP));
     unsigned char* tabs = take((size_t)strips * sizeof(StripTab<T>));
     unsigned char* part = take((size_t)strips * 6 * sizeof(double));
-    unsigned char* st = take(3 * sizeof(StripState));
+    unsigned char* st = take(2 * sizeof(StripState));
+    unsigned char* large = take(sizeof(LargeState));
     if (S) {
         S->strips = strips;
-        S->x0 = x0;
-        S->x1 = x1;
+        for (int b = 0; b < 4; ++b) S->x[b] = x + (size_t)b * buf;
+        S->slot_elems = (long long)(buf / sizeof(T));
+        S->large = reinterpret_cast<LargeState*>(large);
         S->cols = cols;
         S->tabs = tabs;
         S->part = reinterpret_cast<double*>(part);
         S->st = reinterpret_cast<StripState*>(st);
-        S->fin = S->st + 2;
     }
     return o;
 }
@@ -264,14 +274,11 @@ int set_strip_attributes() {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)strip_lds<float>(kStripMaxNodes));
     e |= (int)hipFuncSetAttribute(reinterpret_cast<const void*>(&strip_update<double>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)strip_lds<double>(kStripMaxNodes));
-    e |= (int)hipFuncSetAttribute(strip_finish_f32(), hipFuncAttributeMaxDynamicSharedMemorySize, kGlobalLds);
-    e |= (int)hipFuncSetAttribute(strip_finish_f64(), hipFuncAttributeMaxDynamicSharedMemorySize, kGlobalLds);
     return e;
 }
 
 int launch_strips(int dtype, const StripJob& job, hipStream_t stream) {
-    return dtype == CFSIM_F64 ? launch_t<double>(job, strip_finish_f64(), stream)
-                              : launch_t<float>(job, strip_finish_f32(), stream);
+    return dtype == CFSIM_F64 ? launch_t<double>(job, stream) : launch_t<float>(job, stream);
 }
 
 }  // namespace cfsim
