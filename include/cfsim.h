@@ -231,7 +231,8 @@ cfsim_status cfsim_score(cfsim_context* ctx, const cfsim_graph* A, const cfsim_g
  * workspace is a static device array of CFSIM_NOALLOC_SCRATCH_BYTES that
  * each GPU holds until the process ends (its address is taken once per
  * device by cfsim_context_create).  The call allocates nothing: a pair whose
- * cfsim_score_workspace_size exceeds CFSIM_NOALLOC_SCRATCH_BYTES (FP64
+ * two iterates (resized: cfsim_score_workspace_size) exceed
+ * CFSIM_NOALLOC_SCRATCH_BYTES (FP64
  * beyond about 1,000 x 1,000 nodes, FP32 beyond about 1,400 x 1,400; less
  * when resized or with CFSIM_FLAG_FP64_FINAL) returns CFSIM_E_UNSUPPORTED
  * before any HIP call.  Every call on one GPU shares that GPU's scratch and
@@ -274,8 +275,8 @@ cfsim_status cfsim_score_batch(cfsim_context* ctx, const cfsim_graph_set* set,
  * thousands of nodes): same arguments, outputs and per-pair semantics as
  * cfsim_score_batch, for pairs whose lists do not fit the batched kernels
  * (those report CFSIM_INVALID_INPUT there).  The iterates live in the
- * workspace (HBM); every update is one launch over the tiles of all pairs of
- * the call, followed by a per-pair reduction launch; the whole sequence
+ * workspace (HBM); every update is one launch over the strips (resized: the
+ * tiles) of all pairs of the call, followed by a per-pair reduction launch; the whole sequence
  * (about 2 * max_iter launches, 3 * max_iter with resize) is captured once
  * into a HIP graph cached in the context.  This tiled path also serves every resized pair (opt->resize =
  * CFSIM_RESIZE_BILINEAR) of cfsim_score and cfsim_score_batch.  Limits:

@@ -271,13 +271,21 @@ void append_key(std::vector<unsigned char>& k, const X& x) {
 //   | without resize: strip lists and tables per pair
 int large_nslots(const cfsim_options* o) { return o->resize == CFSIM_RESIZE_BILINEAR ? 6 : 4; }
 
-size_t large_ws_bytes(int64_t n_pairs, int max_nodes, int esize, int nslots) {
-    const size_t parts = (size_t)n_pairs * (size_t)cfsim::large_parts(max_nodes);
+// Whether plain pairs of a call run on strips (given the room for them).
+bool large_strips(const cfsim_options* o, int max_nodes) {
+    return large_nslots(o) == 4 && !mfma_bf16(o) && cfsim::large_on_strips(max_nodes, esize_of(o->dtype));
+}
+size_t large_part_count(int64_t n_pairs, int max_nodes, bool strips) {
+    return (size_t)n_pairs * (size_t)(strips ? cfsim::large_parts(max_nodes) : cfsim::large_tiles(max_nodes));
+}
+
+size_t large_ws_bytes(int64_t n_pairs, int max_nodes, int esize, int nslots, bool strips) {
+    const size_t parts = large_part_count(n_pairs, max_nodes, strips);
     return align256((size_t)n_pairs * sizeof(cfsim::LargeState)) + align256((size_t)(n_pairs + 1) * 8) +
            2 * align256(parts * 8) + align256(parts * 4) +
            align256((size_t)n_pairs * 2 * max_nodes * cfsim::large_rec_bytes(esize)) +
            align256((size_t)n_pairs * nslots * (size_t)global_slot_elems(max_nodes) * (size_t)esize) +
-           (nslots == 4 ? (size_t)n_pairs * align256(cfsim::large_strip_bytes(max_nodes, esize)) : 0);
+           (strips ? (size_t)n_pairs * align256(cfsim::large_strip_bytes(max_nodes, esize)) : 0);
 }
 
 // MFMA variant, after the tiled-path workspace: block lists [n_pairs][2][idx
@@ -292,7 +300,8 @@ size_t mfma_ws_bytes(int64_t n_pairs, int max_nodes) {
 
 // Options, outputs and workspace of a tiled-path launch (pairs filled by the caller).
 cfsim::LargeJob large_job(const cfsim_options* opt, int64_t n_pairs, int max_nodes, cfsim_pair_result* res,
-                          int32_t* match, const int64_t* match_off, void* S_out, const int64_t* S_off, void* ws) {
+                          int32_t* match, const int64_t* match_off, void* S_out, const int64_t* S_off, void* ws,
+                          bool strips) {
     cfsim::LargeJob J{};
     J.n_pairs = (int)n_pairs;
     J.max_nodes = max_nodes;
@@ -306,7 +315,7 @@ cfsim::LargeJob large_job(const cfsim_options* opt, int64_t n_pairs, int max_nod
     J.S_out = S_out;
     J.S_off = S_off;
     unsigned char* p = static_cast<unsigned char*>(ws);
-    const size_t tiles = (size_t)n_pairs * (size_t)cfsim::large_parts(max_nodes);
+    const size_t tiles = large_part_count(n_pairs, max_nodes, strips);
     J.st = reinterpret_cast<cfsim::LargeState*>(p);
     p += align256((size_t)n_pairs * sizeof(cfsim::LargeState));
     J.tile_off = reinterpret_cast<long long*>(p);
@@ -323,8 +332,8 @@ cfsim::LargeJob large_job(const cfsim_options* opt, int64_t n_pairs, int max_nod
     J.nslots = large_nslots(opt);
     J.slot_elems = global_slot_elems(max_nodes);
     p += align256((size_t)n_pairs * J.nslots * (size_t)J.slot_elems * (size_t)esize_of(opt->dtype));
-    if (J.nslots == 4) {
-        J.strips = !mfma_bf16(opt) && cfsim::large_on_strips(max_nodes, esize_of(opt->dtype));
+    if (strips) {
+        J.strips = 1;
         J.strip_area = p;
         J.strip_stride = (long long)align256(cfsim::large_strip_bytes(max_nodes, esize_of(opt->dtype)));
         p += (size_t)n_pairs * (size_t)J.strip_stride;
@@ -610,7 +619,7 @@ size_t cfsim_score_workspace_size(const cfsim_context* ctx, int32_t n_a, int32_t
     (void)ctx;
     if (n_a < 1 || n_b < 1 || !opt) return 0;
     const size_t esize = fp64_final(opt) ? 8 : esize_of(opt->dtype);
-    if (opt->resize == CFSIM_RESIZE_BILINEAR) return large_ws_bytes(1, n_a > n_b ? n_a : n_b, (int)esize, 6);
+    if (opt->resize == CFSIM_RESIZE_BILINEAR) return large_ws_bytes(1, n_a > n_b ? n_a : n_b, (int)esize, 6, false);
     const size_t least = score_ws_min(n_a, n_b, opt);
     if (least < ((size_t)64 << 10)) return least;  // always in LDS
     // the strip path's buffers, lists and tables
@@ -669,7 +678,7 @@ cfsim_status cfsim_score(cfsim_context* ctx, const cfsim_graph* A, const cfsim_g
                 return ok();
             }
         }
-        cfsim::LargeJob J = large_job(opt, 1, M, res, match_out, nullptr, S_out, nullptr, ws);
+        cfsim::LargeJob J = large_job(opt, 1, M, res, match_out, nullptr, S_out, nullptr, ws, false);
         J.single = 1;
         J.ga = ref_of(A);
         J.gb = ref_of(B);
@@ -760,7 +769,7 @@ size_t cfsim_batch_workspace_size(const cfsim_context* ctx, const cfsim_graph_se
     if (opt->resize == CFSIM_RESIZE_BILINEAR) {
         if (set->max_nodes > cfsim::kLargeMaxNodes) return 0;
         // the tiled path's workspace, then the LDS kernels' schedule
-        return large_ws_bytes(n_pairs > 0 ? n_pairs : 1, set->max_nodes, esize_of(opt->dtype), 6) +
+        return large_ws_bytes(n_pairs > 0 ? n_pairs : 1, set->max_nodes, esize_of(opt->dtype), 6, false) +
                sched_ws_bytes(n_pairs) + resized_slots_bytes(ctx, esize_of(opt->dtype), set->max_nodes);
     }
     return batch_ws_bytes(ctx, n_pairs, fp64_final(opt) ? 8 : esize_of(opt->dtype), set->max_nodes);
@@ -896,8 +905,9 @@ static int enqueue_batch(cfsim_context* ctx, const cfsim_graph_set* set, const i
 static int enqueue_large(cfsim_context* ctx, const cfsim_graph_set* set, const int32_t* pair_a,
                          const int32_t* pair_b, int64_t n_pairs, const cfsim_options* opt, cfsim_pair_result* res,
                          int32_t* match, const int64_t* match_off, void* S_out, const int64_t* S_off, void* ws,
-                         hipStream_t st) {
-    cfsim::LargeJob J = large_job(opt, n_pairs, set->max_nodes, res, match, match_off, S_out, S_off, ws);
+                         bool strips, hipStream_t st) {
+    cfsim::LargeJob J = large_job(opt, n_pairs, set->max_nodes, res, match, match_off, S_out, S_off, ws,
+                                  strips);
     J.set = ref_of(set);
     J.pair_a = pair_a;
     J.pair_b = pair_b;
@@ -911,13 +921,14 @@ static int enqueue_resized(cfsim_context* ctx, const cfsim_graph_set* set, const
                            const int32_t* pair_b, int64_t n_pairs, const cfsim_options* opt, cfsim_pair_result* res,
                            int32_t* match, const int64_t* match_off, void* S_out, const int64_t* S_off, void* ws,
                            hipStream_t st) {
-    const size_t lb = large_ws_bytes(n_pairs, set->max_nodes, esize_of(opt->dtype), 6);
+    const size_t lb = large_ws_bytes(n_pairs, set->max_nodes, esize_of(opt->dtype), 6, false);
     BatchWs b = carve_sched(static_cast<unsigned char*>(ws) + lb, n_pairs);
     b.slots[cfsim::kBucketGlobal] = static_cast<unsigned char*>(ws) + lb + sched_ws_bytes(n_pairs);
     int e = enqueue_pass(ctx, set, pair_a, pair_b, n_pairs, opt, opt->dtype, nullptr, res, match, match_off, S_out,
                          S_off, b, st, false, CkptOut{nullptr, nullptr, 0}, Damping{0, 0.0, nullptr, nullptr}, 1);
     if (e != 0) return e;
-    cfsim::LargeJob J = large_job(opt, n_pairs, set->max_nodes, res, match, match_off, S_out, S_off, ws);
+    cfsim::LargeJob J = large_job(opt, n_pairs, set->max_nodes, res, match, match_off, S_out, S_off, ws,
+                                  false);
     J.set = ref_of(set);
     J.pair_a = pair_a;
     J.pair_b = pair_b;
@@ -929,16 +940,18 @@ static int enqueue_resized(cfsim_context* ctx, const cfsim_graph_set* set, const
 static cfsim_status run_large(cfsim_context* ctx, const cfsim_graph_set* set, const int32_t* pair_a,
                               const int32_t* pair_b, int64_t n_pairs, const cfsim_options* opt,
                               cfsim_pair_result* res, int32_t* match, const int64_t* match_off, void* S_out,
-                              const int64_t* S_off, void* ws, hipStream_t st) {
+                              const int64_t* S_off, void* ws, bool strips, hipStream_t st) {
     if (graphs_disabled()) {
         const int e = enqueue_large(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws,
-                                    st);
+                                    strips, st);
         if (e != 0) return hip_fail(e, "tiled-path launch");
         return ok();
     }
-    const auto key = set_call_key(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws);
+    auto key = set_call_key(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws);
+    append_key(key, strips);
     return replay_or_capture(ctx, &ctx->large_graph, &ctx->large_exec, &ctx->large_key, key, st, [&](hipStream_t cs) {
-        return enqueue_large(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws, cs);
+        return enqueue_large(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws, strips,
+                             cs);
     });
 }
 
@@ -1134,7 +1147,8 @@ size_t cfsim_large_workspace_size(const cfsim_context* ctx, const cfsim_graph_se
                                   const cfsim_options* opt) {
     (void)ctx;
     if (n_pairs < 1 || !set || !opt || set->max_nodes < 1 || set->max_nodes > cfsim::kLargeMaxNodes) return 0;
-    size_t b = large_ws_bytes(n_pairs, set->max_nodes, esize_of(opt->dtype), large_nslots(opt));
+    size_t b = large_ws_bytes(n_pairs, set->max_nodes, esize_of(opt->dtype), large_nslots(opt),
+                              large_strips(opt, set->max_nodes));
     if (mfma_bf16(opt)) b += mfma_ws_bytes(n_pairs, set->max_nodes);
     return b;
 }
@@ -1160,12 +1174,18 @@ cfsim_status cfsim_score_large(cfsim_context* ctx, const cfsim_graph_set* set, c
         if (!ctx) return fail(CFSIM_E_INVALID_ARG, "context is NULL");
         return ok();
     }
-    const size_t need = cfsim_large_workspace_size(ctx, set, n_pairs, opt);
+    // strips with the workspace that the size function names; without the room
+    // for their lists the tiles
+    const size_t full = cfsim_large_workspace_size(ctx, set, n_pairs, opt);
+    const bool strips = large_strips(opt, set->max_nodes) && ws_bytes >= full;
+    const size_t need = large_strips(opt, set->max_nodes)
+                            ? large_ws_bytes(n_pairs, set->max_nodes, esize_of(opt->dtype), 4, false)
+                            : full;
     if (ws_bytes < need || !ws) return fail(CFSIM_E_WORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, need);
     if (!ctx) return fail(CFSIM_E_INVALID_ARG, "context is NULL");
     int e = (int)hipSetDevice(ctx->device);
     if (e != 0) return hip_fail(e, "hipSetDevice");
-    return run_large(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws,
+    return run_large(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws, strips,
                      static_cast<hipStream_t>(stream));
 }
 
