@@ -63,8 +63,43 @@ struct EvenSums {
     double nu2, dy2, dyy;
 };
 
-// Block reduction of the three even-step sums (red holds 3 * NW doubles).
+// Sums of NW consecutive doubles of LDS per 16-lane row (NW <= 16): lane l
+// brings x = area[l & (NW - 1)] of its row's area.
 template <int NW>
+__device__ __forceinline__ double row_sums(double x) {
+    if constexpr (NW > 1) x += dpp<kDppXor1>(x);
+    if constexpr (NW > 2) x += dpp<kDppXor2>(x);
+    if constexpr (NW > 4) x += dpp<kDppHalfMirror>(x);
+    if constexpr (NW > 8) x += dpp<kDppMirror>(x);
+    return x;
+}
+
+// Whether an update's closing arithmetic is the short form below.  Every wave
+// repeats what follows the reduction (sums over the waves, 1 / nu, the test):
+// the short form takes a 97 x 121 FP32 pair from 1,140 to 1,078 us, all pairs of
+// 256 graphs from 72.1 to 70.2 ms, of 128 resized ones from 40.6 to 39.3 ms.
+// FP32: the waves' partials are summed by lane moves, 1 / nu comes from
+// v_rsq_f64 and one third-order step (0.50 ulp of FP64 at most where the root
+// and the division have 1.42), square roots are left to the end.  FP64 keeps the order of
+// the sums and the two roundings of 1 / sqrt: its scale's last bit shows in S.
+template <typename T>
+constexpr bool kShortTail = sizeof(T) == 4;
+
+// Block sum of an odd update.
+template <typename T, int NW>
+__device__ __forceinline__ double block_norm(double x, double* red) {
+    if constexpr (!kShortTail<T>) {
+        return block_sum<NW>(x, red);
+    } else {
+        x = wave_sum(x);
+        if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = x;
+        __syncthreads();
+        return lane_value(row_sums<NW>(red[threadIdx.x & (NW - 1)]), 0);
+    }
+}
+
+// Block reduction of the three even-step sums (red holds 3 * NW doubles).
+template <typename T, int NW>
 __device__ inline EvenSums block_sum_even(EvenSums s, double* red) {
     s.nu2 = wave_sum(s.nu2);
     s.dy2 = wave_sum(s.dy2);
@@ -77,19 +112,44 @@ __device__ inline EvenSums block_sum_even(EvenSums s, double* red) {
     }
     __syncthreads();
     EvenSums t{0.0, 0.0, 0.0};
-    for (int w = 0; w < NW; ++w) {
-        t.nu2 += red[w];
-        t.dy2 += red[NW + w];
-        t.dyy += red[2 * NW + w];
+    if constexpr (kShortTail<T>) {
+        const int lane = (int)(threadIdx.x & (kWave - 1));
+        const double x = row_sums<NW>(red[min(lane >> 4, 2) * NW + (lane & (NW - 1))]);
+        t.nu2 = lane_value(x, 0);
+        t.dy2 = lane_value(x, 16);
+        t.dyy = lane_value(x, 32);
+    } else {
+        for (int w = 0; w < NW; ++w) {
+            t.nu2 += red[w];
+            t.dy2 += red[NW + w];
+            t.dyy += red[2 * NW + w];
+        }
     }
     return t;
 }
 
-// ||S_k - S_{k-2}|| from the even-step sums (a = 1/nu_{k-2}, inv = 1/nu_k).
-__device__ inline double even_step_delta(const EvenSums& t, double a, double inv) {
+// 1 / sqrt(tot).
+template <typename T>
+__device__ __forceinline__ double inv_norm(double tot) {
+    if constexpr (!kShortTail<T>) {
+        return 1.0 / sqrt(tot);
+    } else {
+        const double y = __builtin_amdgcn_rsq(tot);  // relative error below 2^-22
+        const double h = tot * y;
+        const double e = fma(-fma(tot, y, -h), y, fma(-h, y, 1.0));  // 1 - tot y^2
+        return fma(y * e, fma(0.375, e, 0.5), y);
+    }
+}
+
+// ||S_k - S_{k-2}||^2 from the even-step sums (a = 1/nu_{k-2}, inv = 1/nu_k).
+__device__ inline double even_step_change(const EvenSums& t, double a, double inv) {
     const double b = inv - a;
     const double d2 = a * a * t.dy2 + 2.0 * a * b * t.dyy + b * b * t.nu2;
-    return sqrt(fmax(d2, 0.0));
+    return fmax(d2, 0.0);
+}
+// sqrt(d2) < tol, without the root while the change is far above.
+__device__ __forceinline__ bool change_below(double d2, double tol) {
+    return d2 <= 4.0 * tol * tol && sqrt(d2) < tol;
 }
 
 // Per-entry part of the even-step sums: y_new is the entry written, y_old the
@@ -288,6 +348,7 @@ __device__ __forceinline__ IterOut iterate_lds(const PairJob& J, unsigned char* 
     int cur = 0;
     T sigma = T(1);
     double a_even = 1.0;  // 1/nu of the last even iterate (S_0 is stored normalised)
+    double nu2 = 0.0, d2 = -1.0;  // nu^2 of the last update, delta^2 of the last even one
     for (int k = 1; k <= J.max_iter; ++k) {
         const bool even = (k & 1) == 0;
         EvenSums es{0.0, 0.0, 0.0};
@@ -297,15 +358,15 @@ __device__ __forceinline__ IterOut iterate_lds(const PairJob& J, unsigned char* 
             lds_rows<false, T, NT, NCH>(Sb, Nb, rowb, nR, G, L, ovf, any_ovf, col, cv, sigma, es, G.rstate, seg);
         double tot;
         if (even)
-            es = block_sum_even<NW>(es, red);
-        tot = even ? es.nu2 : block_sum<NW>(es.nu2, red + 3 * NW);
+            es = block_sum_even<T, NW>(es, red);
+        tot = even ? es.nu2 : block_norm<T, NW>(es.nu2, red + 3 * NW);
         if (!(tot > 0.0) || !isfinite(tot)) {  // cannot normalise: keep S_{k-1}
             out.status = CFSIM_DEGENERATE;
             break;
         }
-        out.nu = sqrt(tot);
+        nu2 = tot;
         out.iters = k;
-        const double inv = 1.0 / out.nu;
+        const double inv = inv_norm<T>(tot);
         sigma = T(inv);
         {
             const unsigned char* t = Sb;
@@ -317,14 +378,16 @@ __device__ __forceinline__ IterOut iterate_lds(const PairJob& J, unsigned char* 
             write_checkpoint<T, NT>(ck + (long long)(k / J.ckpt_every - 1) * nR * nC, Sb, sigma, (long long)nR * nC,
                                     sh.swap ? nR : nC, nC, sh.swap != 0);
         if (even) {
-            out.delta = even_step_delta(es, a_even, inv);
+            d2 = even_step_change(es, a_even, inv);
             a_even = inv;
-            if (out.delta < J.tol) {
+            if (change_below(d2, J.tol)) {
                 out.status = CFSIM_CONVERGED;
                 break;
             }
         }
     }
+    if (nu2 > 0.0) out.nu = sqrt(nu2);
+    if (d2 >= 0.0) out.delta = sqrt(d2);
     if (out.status == 0) out.status = CFSIM_HIT_MAX_ITER;
     if (sigma != T(1)) {  // S = sigma * Y (sigma is the same in every thread)
         T* Sw = reinterpret_cast<T*>(const_cast<unsigned char*>(Sb));
@@ -360,6 +423,7 @@ __device__ __forceinline__ IterOut iterate_global(const PairJob& J, const PairSh
     int cur = 0;
     T sigma = T(1);
     double a_even = 1.0;
+    double nu2 = 0.0, d2 = -1.0;  // nu^2 of the last update, delta^2 of the last even one
     const int last = nR - 1;
     for (int k = 1; k <= J.max_iter; ++k) {
         const bool even = (k & 1) == 0;
@@ -387,15 +451,15 @@ __device__ __forceinline__ IterOut iterate_global(const PairJob& J, const PairSh
             }
         }
         if (even)
-            es = block_sum_even<NW>(es, red);
-        const double tot = even ? es.nu2 : block_sum<NW>(es.nu2, red + 3 * NW);
+            es = block_sum_even<T, NW>(es, red);
+        const double tot = even ? es.nu2 : block_norm<T, NW>(es.nu2, red + 3 * NW);
         if (!(tot > 0.0) || !isfinite(tot)) {
             out.status = CFSIM_DEGENERATE;
             break;
         }
-        out.nu = sqrt(tot);
+        nu2 = tot;
         out.iters = k;
-        const double inv = 1.0 / out.nu;
+        const double inv = inv_norm<T>(tot);
         sigma = T(inv);
         {
             const unsigned char* t = Sb;
@@ -407,14 +471,16 @@ __device__ __forceinline__ IterOut iterate_global(const PairJob& J, const PairSh
             write_checkpoint<T, NT>(ck + (long long)(k / J.ckpt_every - 1) * nR * nC, Sb, sigma, (long long)nR * nC,
                                     sh.swap ? nR : nC, nC, sh.swap != 0);
         if (even) {
-            out.delta = even_step_delta(es, a_even, inv);
+            d2 = even_step_change(es, a_even, inv);
             a_even = inv;
-            if (out.delta < J.tol) {
+            if (change_below(d2, J.tol)) {
                 out.status = CFSIM_CONVERGED;
                 break;
             }
         }
     }
+    if (nu2 > 0.0) out.nu = sqrt(nu2);
+    if (d2 >= 0.0) out.delta = sqrt(d2);
     if (out.status == 0) out.status = CFSIM_HIT_MAX_ITER;
     if (sigma != T(1)) {
         T* Sw = reinterpret_cast<T*>(const_cast<unsigned char*>(Sb));
@@ -473,6 +539,7 @@ __device__ __forceinline__ IterOut iterate_strips(const PairJob& J, const PairSh
     int cur = 0;
     T sigma = T(1);
     double a_even = 1.0;  // 1/nu of the last even iterate (S_0 is stored normalised)
+    double nu2 = 0.0, d2 = -1.0;  // nu^2 of the last update, delta^2 of the last even one
     for (int k = 1; k <= J.max_iter; ++k) {
         const bool even = (k & 1) == 0;
         EvenSums es{0.0, 0.0, 0.0};
@@ -516,15 +583,15 @@ __device__ __forceinline__ IterOut iterate_strips(const PairJob& J, const PairSh
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
         if (even)
-            es = block_sum_even<NW>(es, red);
-        const double tot = even ? es.nu2 : block_sum<NW>(es.nu2, red + 3 * NW);
+            es = block_sum_even<T, NW>(es, red);
+        const double tot = even ? es.nu2 : block_norm<T, NW>(es.nu2, red + 3 * NW);
         if (!(tot > 0.0) || !isfinite(tot)) {  // cannot normalise: keep S_{k-1}
             out.status = CFSIM_DEGENERATE;
             break;
         }
-        out.nu = sqrt(tot);
+        nu2 = tot;
         out.iters = k;
-        const double inv = 1.0 / out.nu;
+        const double inv = inv_norm<T>(tot);
         sigma = T(inv);
         T* t = Xc;
         Xc = Xn;
@@ -541,14 +608,16 @@ __device__ __forceinline__ IterOut iterate_strips(const PairJob& J, const PairSh
             }
         }
         if (even) {
-            out.delta = even_step_delta(es, a_even, inv);
+            d2 = even_step_change(es, a_even, inv);
             a_even = inv;
-            if (out.delta < J.tol) {
+            if (change_below(d2, J.tol)) {
                 out.status = CFSIM_CONVERGED;
                 break;
             }
         }
     }
+    if (nu2 > 0.0) out.nu = sqrt(nu2);
+    if (d2 >= 0.0) out.delta = sqrt(d2);
     if (out.status == 0) out.status = CFSIM_HIT_MAX_ITER;
     // S = sigma X^T into the other buffer, in 32 x 32 tiles through LDS
     __syncthreads();
@@ -932,6 +1001,7 @@ __device__ __forceinline__ IterOut iterate_resized(const PairJob& J, unsigned ch
     }
     T sigma = T(1);
     double a_even = 1.0;  // 1/nu of the last even iterate (U_0 belongs to nu_0 = 1)
+    double nu2 = 0.0, d2 = -1.0;  // nu^2 of the last update, delta^2 of the last even one
     for (int k = 1; k <= J.max_iter; ++k) {
         const bool even = (k & 1) == 0, last = k == J.max_iter;
         EvenSums es{0.0, 0.0, 0.0};
@@ -946,23 +1016,23 @@ __device__ __forceinline__ IterOut iterate_resized(const PairJob& J, unsigned ch
                                                    sigma, es);
         double tot;
         if (even)
-            es = block_sum_even<NW>(es, red);
-        tot = even ? es.nu2 : block_sum<NW>(es.nu2, red + 3 * NW);
+            es = block_sum_even<T, NW>(es, red);
+        tot = even ? es.nu2 : block_norm<T, NW>(es.nu2, red + 3 * NW);
         if (!(tot > 0.0) || !isfinite(tot)) {
             out.status = CFSIM_DEGENERATE;
             break;
         }
-        out.nu = sqrt(tot);
+        nu2 = tot;
         out.iters = k;
-        const double inv = 1.0 / out.nu;
+        const double inv = inv_norm<T>(tot);
         sigma = T(inv);
         unsigned char* t = Vc;
         Vc = Vn;
         Vn = t;
         if (even) {
-            out.delta = even_step_delta(es, a_even, inv);
+            d2 = even_step_change(es, a_even, inv);
             a_even = inv;
-            if (out.delta < J.tol) {
+            if (change_below(d2, J.tol)) {
                 out.status = CFSIM_CONVERGED;
                 break;
             }
@@ -970,6 +1040,8 @@ __device__ __forceinline__ IterOut iterate_resized(const PairJob& J, unsigned ch
             // the last update is odd: U_k stands in Ue and the loop ends
         }
     }
+    if (nu2 > 0.0) out.nu = sqrt(nu2);
+    if (d2 >= 0.0) out.delta = sqrt(d2);
     if (out.status == 0) out.status = CFSIM_HIT_MAX_ITER;
     return out;
 }
