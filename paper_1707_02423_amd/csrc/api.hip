@@ -793,6 +793,26 @@ struct Damping {
     const int64_t* prior_off;
 };
 
+// Whether a set can have pairs past a workgroup's LDS: no LDS kernel holds two
+// graphs of its largest size and mean number of jumps per node.  (Where the
+// mean misjudges a graph, its pairs run in line or the branch is empty.)  An
+// empty branch costs 15-20 us (3 pairs of 8-40 nodes at 2 updates: 176 us in
+// line, 197 with it), and in a resized call, whose 600 launches of the tiled
+// path each take longer in a graph that is no chain, 0.7 ms (91 FP32 pairs of
+// 7-76 nodes: 6.8 ms in line, 7.55 with it).  With such pairs it gains: 28
+// resized FP32 pairs of 8-150 nodes 21.5 ms in line, 16.5 with it.
+int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize) {
+    const int n = set->max_nodes, esize = esize_of(dtype);
+    const double jumps = (double)set->total_edges / (double)(set->total_nodes > 0 ? set->total_nodes : 1);
+    const int nnz = (int)std::fmin(std::ceil(jumps * n), 1e8);
+    for (int v = 0; v < cfsim::kNumVariants; ++v) {
+        cfsim::PairShape sh;
+        if (resize ? cfsim::resized_fits(n, n, nnz, nnz, v, esize) : cfsim::choose_shape(n, n, nnz, nnz, v, esize, &sh))
+            return 0;
+    }
+    return 1;
+}
+
 static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const int32_t* pair_a, const int32_t* pair_b,
                         int64_t n_pairs, const cfsim_options* opt, int dtype, const cfsim_pair_result* filter,
                         cfsim_pair_result* res, int32_t* match, const int64_t* match_off, void* S_out,
@@ -842,8 +862,9 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
     // device: a bucket's persistent grid drains its queue longest pair first,
     // so its tail is about one pair long.  The global-memory bucket holds the
     // largest pairs, often fewer than CUs; in a captured call it runs beside
-    // the others on a branch of the graph, started first.
-    const bool branch = st == ctx->cap && !timed;
+    // the others on a branch of the graph, started first, unless the set has
+    // no pair for it.
+    const bool branch = st == ctx->cap && !timed && cfsim_route_branch(set, dtype, resize);
     if (branch) {
         if ((e = (int)hipEventRecord(ctx->fork, st)) != 0) return e;
         if ((e = (int)hipStreamWaitEvent(ctx->side, ctx->fork, 0)) != 0) return e;

@@ -524,3 +524,9 @@ constexpr int kWardMaxObs = 4096;
 int launch_ward(const double* X, int n, int f, double* Z, double* D, hipStream_t stream);
 
 }  // namespace cfsim
+
+// Host rules that choose between the routes of a call (api.hip).  They are no
+// part of the ABI of cfsim.h; C linkage so that tests can ask them without a GPU.
+extern "C" {
+int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize);
+}
