@@ -72,7 +72,7 @@ __device__ void backward_pair(const BwdJob& J, int p, unsigned char* smem, doubl
     bool ok = bwd_pair(J, p, &A, &B);
     if (ok) {
         bs = bwd_shape(A, B, (int)sizeof(T));
-        if (J.strips && bwd_on_strips(A, B, bs)) return;
+        if (bwd_on_strips(J, A, B, bs)) return;
         sh = make_shape(A.n, B.n, 0, NW);  // S kept as n_B x n_A: R = B, C = A
         ok = bs.fits;
     }
@@ -318,10 +318,10 @@ int launch_backward(int dtype, const SetRef& set, const int32_t* pair_a, const i
     // the strips path where it fits the workspace of the other: the size does
     // not depend on the route
     const size_t strip_ws = fck ? bwd_strips_bytes(max_nodes, n_pairs, grid, ckpt, esize) : 0;
-    J.strips = strip_ws != 0 && ws_bytes >= strip_ws;
+    J.strip_nodes = strip_ws != 0 && ws_bytes >= strip_ws ? max_nodes : 0;
     J.ws = ws;
     int e = 0;
-    if (J.strips && (e = launch_bwd_strips(dtype, J, max_nodes, grid / 2, stream)) != 0) return e;
+    if (J.strip_nodes && (e = launch_bwd_strips(dtype, J, max_nodes, grid / 2, stream)) != 0) return e;
     // queue counter in front of the slots
     J.queue = static_cast<int32_t*>(ws);
     J.ws = static_cast<unsigned char*>(ws) + 256;

@@ -29,7 +29,7 @@ struct BwdJob {
     void* ws;              // gridDim.x slots of slot_bytes
     long long slot_elems, slot_bytes;
     int32_t* queue;
-    int strips;            // the pairs bwd_on_strips() takes are done elsewhere
+    int strip_nodes;       // the pairs bwd_on_strips() takes are done elsewhere (0: none)
 };
 
 // LDS of the one-workgroup kernel: lists | gA, gB | edge sources | per-wave
@@ -62,10 +62,12 @@ __device__ inline bool bwd_pair(const BwdJob& J, int p, GraphRef* A, GraphRef* B
 }
 
 // Pairs of the strips path: A edges within the lanes (the order of the partial
-// sums is then the other kernel's) and a strip of B's nodes within LDS.
+// sums is then the other kernel's) and both graphs within the node count that
+// the call's tables and its strips' LDS are laid out for (its max_nodes; a
+// graph above it may still fit the other kernel's slot).
 constexpr int kBwdStripNodes = 512;
-__device__ inline bool bwd_on_strips(const GraphRef& A, const GraphRef& B, const BwdShape& s) {
-    return s.fits && s.lane_edges && B.n <= kBwdStripNodes && A.n <= kBwdStripNodes;
+__device__ inline bool bwd_on_strips(const BwdJob& J, const GraphRef& A, const GraphRef& B, const BwdShape& s) {
+    return s.fits && s.lane_edges && B.n <= J.strip_nodes && A.n <= J.strip_nodes;
 }
 
 // Host side of adjoint_strips.hip (bwd_strips_bytes is its workspace; 0: the path

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kNT) void adj_init(AdjJob A) {
     GraphRef a{}, b{};
     AdjPair st{};
     bool on = bwd_pair(A.J, p, &a, &b);
-    if (on) on = bwd_on_strips(a, b, bwd_shape(a, b, (int)sizeof(T)));
+    if (on) on = bwd_on_strips(A.J, a, b, bwd_shape(a, b, (int)sizeof(T)));
     const double gs = A.J.grad_score[p];
     const cfsim_pair_result* fr = A.J.fwd + p;
     if (on) {

@@ -77,3 +77,22 @@ def test_a_pair_for_every_cu(cf, ctx):
     graphs = [make_cfg(3 + i % 37, Grammar(counts="trip"), seed=i) for i in range(46)]
     a, b = np.triu_indices(46)
     _check(_grads(cf, ctx, graphs, a[:253], b[:253], "f64", 12, 4), "f64")
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_a_graph_above_the_sets_largest_size(cf, ctx, dtype):
+    # 64 x 10 entries fit a slot of 33 x 33, which is all the one-workgroup
+    # kernel asks for; the strips' tables are laid out for 33 nodes
+    graphs = [make_cfg(n, Grammar(counts="trip"), seed=n) for n in (64, 10, 33, 30)]
+    out = []
+    for ck in (0, 8):
+        gs = cf.pack(ctx, graphs)
+        gs.max_nodes = 33
+        b = cf.Batch(ctx, gs, np.array([0, 1, 2], np.int32), np.array([1, 0, 3], np.int32), dtype=dtype, max_iter=24,
+                     tol=0.0, want_match=True, checkpoint_every=ck)
+        b.run()
+        g = torch.zeros(gs.total_edges, dtype=torch.float64, device="cuda")
+        st = cf.backward(b, torch.ones(3, dtype=torch.float64), g, checkpoint_every=8)
+        out.append((g.cpu().numpy(), st.cpu().numpy(), b.results().copy()))
+    assert (out[0][1] == 0).all()
+    _check(out, dtype)
