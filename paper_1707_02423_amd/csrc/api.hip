@@ -609,6 +609,30 @@ static int plain_variant(int nA, int nB, int nnzA, int nnzB, int esize, cfsim::P
     return first;
 }
 
+// Updates to expect before a tolerance stops a pair: of 120 pairs of generated
+// control-flow graphs (8 to 410 nodes) nine in ten made at least 52 at tol 1e-3,
+// 70 at 1e-4, 128 at 1e-6, 350 at 1e-9 and 425 at 1e-12 (the first one of all
+// stopped after 44, 58, 86, 130 and 176): 17 per decade and more.  tol = 0 never
+// stops one.
+static double updates_expected(const cfsim_options* opt) {
+    const double k = opt->tol > 0.0 ? std::fmax(0.0, -17.0 * std::log10(opt->tol)) : opt->max_iter;
+    return std::fmin(k, opt->max_iter);
+}
+
+// Whether a plain pair past LDS runs on strips.  Their launches are enqueued
+// for max_iter updates whenever the pair stops, and an empty one takes 4.0 us,
+// where one workgroup ends with the pair but needs 1.05 ns (FP64 1.65) per entry
+// and update, of which a useful launch on strips leaves a tenth.  Strips are
+// taken where the updates to expect pay for all launches: a 150 x 150 FP32 pair
+// of 200 updates 1.5 ms (5.4 in one workgroup), but with max_iter 1000 and
+// stopped after two 3.1 ms (0.6).
+int cfsim_route_score_strips(int n_a, int n_b, const cfsim_options* opt) {
+    const int largest = n_a > n_b ? n_a : n_b;
+    if (largest > cfsim::kStripMaxNodes || opt->max_iter > cfsim::kStripMaxIter) return 0;
+    const double saved_us = 0.9 * (opt->dtype == CFSIM_F64 ? 1.65e-3 : 1.05e-3) * (double)n_a * (double)n_b;
+    return 4.0 * opt->max_iter <= updates_expected(opt) * saved_us;
+}
+
 static size_t score_ws_min(int32_t n_a, int32_t n_b, const cfsim_options* opt) {
     const size_t esize = fp64_final(opt) ? 8 : esize_of(opt->dtype);
     // the two iterate buffers of the global kernel (the LDS kernels need none)
@@ -719,11 +743,10 @@ cfsim_status cfsim_score(cfsim_context* ctx, const cfsim_graph* A, const cfsim_g
     if (e != 0) return hip_fail(e, "hipSetDevice");
     hipStream_t st = static_cast<hipStream_t>(stream);
     // A pair past LDS runs on strips (one launch per update over the whole
-    // chip) when the workspace holds their buffers and tables, as the workspace
-    // that cfsim_score_workspace_size names does; with less (down to the two
-    // buffers of the global kernel) in one workgroup.
-    const int largest = A->n > B->n ? A->n : B->n;
-    if (variant == cfsim::kBucketGlobal && largest <= cfsim::kStripMaxNodes && opt->max_iter <= cfsim::kStripMaxIter &&
+    // chip) when they pay for it and the workspace holds their buffers and
+    // tables, as the workspace that cfsim_score_workspace_size names does; with
+    // less (down to the two buffers of the global kernel) in one workgroup.
+    if (variant == cfsim::kBucketGlobal && cfsim_route_score_strips(A->n, B->n, opt) &&
         ws_bytes >= cfsim::strip_bytes(A->n, B->n, esize)) {
         cfsim::StripJob S{};
         S.J = job;

@@ -529,4 +529,5 @@ int launch_ward(const double* X, int n, int f, double* Z, double* D, hipStream_t
 // part of the ABI of cfsim.h; C linkage so that tests can ask them without a GPU.
 extern "C" {
 int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize);
+int cfsim_route_score_strips(int n_a, int n_b, const cfsim_options* opt);
 }

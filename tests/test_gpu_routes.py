@@ -1,0 +1,61 @@
+"""The launches a call enqueues: which route it took, and that they do not follow max_iter where a tolerance
+stops the pairs early.  A call is captured into a graph, whose kernel nodes are counted; nothing of it runs."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from cfgsynth import Grammar, make_cfg
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def cfm():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1707_02423_amd import cfsim
+    return cfsim
+
+
+def launches(cfm, call):
+    """Kernels that call(stream) enqueues."""
+    L = cfm.lib()
+    stream = torch.cuda.Stream()
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    assert L.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 2) == 0
+    rc = call(stream.cuda_stream)
+    assert L.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
+    assert rc == 0, L.cfsim_last_error()
+    assert L.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    assert L.hipGraphDestroy(graph) == 0
+    return n.value
+
+
+@pytest.fixture(scope="module")
+def ctx(cfm):
+    return cfm.Context(0)
+
+
+def _score_launches(cfm, ctx, n_a, n_b, dtype, max_iter, tol, ws_bytes=None):
+    gs = cfm.pack(ctx, [make_cfg(n, Grammar(counts="trip"), seed=n) for n in (n_a, n_b)])
+    opt = cfm.options(dtype, max_iter, tol)
+    A, B = gs.graph(0), gs.graph(1)
+    L = cfm.lib()
+    size = ws_bytes or L.cfsim_score_workspace_size(ctx.handle, n_a, n_b, ctypes.byref(opt))
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    match = torch.empty(n_b, dtype=torch.int32, device="cuda")
+    res = torch.empty(cfm.RESULT_BYTES, dtype=torch.uint8, device="cuda")
+    return launches(cfm, lambda s: L.cfsim_score(ctx.handle, ctypes.byref(A), ctypes.byref(B), ctypes.byref(opt), None,
+                                                 match.data_ptr(), res.data_ptr(), ws.data_ptr(), size, s))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_a_single_pairs_launches(cfm, ctx, dtype):
+    assert _score_launches(cfm, ctx, 150, 160, dtype, 200, 1e-12) > 200   # strips
+    assert _score_launches(cfm, ctx, 150, 160, dtype, 2000, 1e-2) == 1    # one workgroup
+    e = 8 if dtype == "f64" else 4
+    assert _score_launches(cfm, ctx, 150, 160, dtype, 200, 1e-12, ws_bytes=2 * 150 * 160 * e + 256) == 1

@@ -22,3 +22,18 @@ def test_a_batch_branches_only_for_pairs_past_lds(dtype, resize, max_nodes, jump
     s = _set(max_nodes, jumps=jumps)
     d = {"f64": cf.F64, "f32": cf.F32}[dtype]
     assert cf.lib().cfsim_route_branch(ctypes.byref(s), d, resize) == branch
+
+
+@pytest.mark.parametrize("dtype,n_a,n_b,max_iter,tol,strips", [
+    ("f32", 150, 150, 200, 1e-12, 1), ("f64", 150, 150, 200, 1e-12, 1), ("f32", 333, 410, 200, 1e-3, 1),
+    ("f32", 150, 150, 200, 1e-3, 1), ("f32", 150, 150, 1000, 1e-12, 1), ("f32", 150, 150, 4096, 0.0, 1),
+    # stopped early: the launches of max_iter updates would not be paid for
+    ("f32", 150, 150, 2000, 1e-2, 0), ("f64", 150, 150, 2000, 1e-2, 0), ("f32", 333, 410, 4096, 1e-2, 0),
+    ("f32", 150, 150, 200, 1.0, 0), ("f32", 150, 150, 1, 1e3, 0),
+    # limits of the strips
+    ("f32", 1024, 24, 200, 0.0, 1), ("f32", 1025, 24, 200, 0.0, 0), ("f32", 24, 1025, 200, 0.0, 0),
+    ("f32", 150, 150, 4097, 0.0, 0),
+])
+def test_a_pair_takes_strips_where_its_updates_pay_for_the_launches(dtype, n_a, n_b, max_iter, tol, strips):
+    opt = cf.options(dtype, max_iter, tol)
+    assert cf.lib().cfsim_route_score_strips(n_a, n_b, ctypes.byref(opt)) == strips
