@@ -645,9 +645,14 @@ size_t cfsim_score_workspace_size(const cfsim_context* ctx, int32_t n_a, int32_t
     const size_t esize = fp64_final(opt) ? 8 : esize_of(opt->dtype);
     if (opt->resize == CFSIM_RESIZE_BILINEAR) return large_ws_bytes(1, n_a > n_b ? n_a : n_b, (int)esize, 6, false);
     const size_t least = score_ws_min(n_a, n_b, opt);
-    if (least < ((size_t)64 << 10)) return least;  // always in LDS
-    // the strip path's buffers, lists and tables
-    const size_t strips = align256(cfsim::strip_bytes(n_a, n_b, (int)esize));
+    // the strip path's buffers, lists and tables, for a pair that takes it: not
+    // one that an LDS kernel holds (asked with four jumps per node, twice a
+    // branch's two; a denser pair that none holds then runs in one workgroup)
+    if (!cfsim_route_score_strips(n_a, n_b, opt)) return least;
+    cfsim::PairShape sh;
+    const int variant = plain_variant(n_a, n_b, 4 * n_a, 4 * n_b, esize_of(opt->dtype), &sh);
+    if (variant >= 0 && variant < cfsim::kNumVariants) return least;
+    const size_t strips = align256(cfsim::strip_bytes(n_a, n_b, esize_of(opt->dtype)));
     return least > strips ? least : strips;
 }
 

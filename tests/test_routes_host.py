@@ -37,3 +37,20 @@ def test_a_batch_branches_only_for_pairs_past_lds(dtype, resize, max_nodes, jump
 def test_a_pair_takes_strips_where_its_updates_pay_for_the_launches(dtype, n_a, n_b, max_iter, tol, strips):
     opt = cf.options(dtype, max_iter, tol)
     assert cf.lib().cfsim_route_score_strips(n_a, n_b, ctypes.byref(opt)) == strips
+
+
+@pytest.mark.parametrize("dtype,n_a,n_b,kw,buffers", [
+    ("f32", 97, 121, {}, 2), ("f64", 90, 80, {}, 2),                      # in LDS
+    ("f32", 150, 150, {}, 4), ("f64", 110, 120, {}, 4), ("f32", 333, 410, {}, 4), ("f32", 1024, 60, {}, 4),
+    ("f32", 1025, 60, {}, 2), ("f32", 3000, 3000, {}, 2), ("f32", 333, 410, dict(max_iter=4097), 2),
+    ("f32", 333, 410, dict(max_iter=4096, tol=1e-2), 2),                   # one workgroup
+    ("f32", 333, 410, dict(fp64_final=True), 4),   # FP32 strips, or two FP64 iterates: the same size but for the lists
+    ("f32", 97, 121, dict(fp64_final=True), 4),    # two FP64 iterates
+])
+def test_the_workspace_of_a_pair_is_that_of_its_route(dtype, n_a, n_b, kw, buffers):
+    opt = cf.options(dtype, **kw)
+    size = cf.lib().cfsim_score_workspace_size(None, n_a, n_b, ctypes.byref(opt))
+    one = n_a * n_b * (8 if dtype == "f64" else 4)
+    # strips keep lists of 56 (FP64: 96) bytes per column and tables of 496 (1,152) per four rows beside their iterates
+    lists = 200 * (n_a + n_b + 64) * (2 if dtype == "f64" else 1)
+    assert buffers * one <= size <= buffers * one + (lists if buffers == 4 else 256)
