@@ -905,6 +905,7 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
         job.queue = b.queues + v;
         job.variant = v;
         int grid = 1;
+        bool whole_cu = false;
         if (v < cfsim::kNumVariants) {
             job.gws = nullptr;  // both iterates stay in LDS
             job.slot_elems = 0;
@@ -913,9 +914,20 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
             job.gws = b.slots[v];
             job.slot_elems = resize ? cfsim::resized_slot_elems(set->max_nodes) : global_slot_elems(set->max_nodes);
             grid = ctx->grid[d][v];
-            if (resize || dm.on) {
+            // Up to one pair per CU: one workgroup per CU, which takes its whole
+            // LDS.  Two that share a CU while others idle slow each other down, and
+            // whether the dispatcher places them so depends on what ran before:
+            // 190 FP64 pairs of 200 nodes 27.8 ms with two per CU, 23.1 with one
+            // (23.4-25.7 behind the LDS kernels' launches, before the branch); 28
+            // damped FP32 ones 22.5-23.8 / 19.7.  Resized pairs, whose call has
+            // LDS and tiled pairs beside them: 28.6 with two, 30.5 with one.
+            if (!resize && n_pairs <= num_cus_of(ctx)) {
+                grid = num_cus_of(ctx);
+                whole_cu = true;
+            } else if (resize || dm.on) {
                 grid = num_cus_of(ctx) * lds_blocks_per_cu(v, esize);
-            } else {
+            }
+            if (!resize && !dm.on) {
                 // one workgroup per CU; the slots of the others hold the strip tables
                 const long long slot = 2 * job.slot_elems * esize;
                 const int slots = num_cus_of(ctx) * lds_blocks_per_cu(v, esize);
@@ -925,7 +937,7 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
         }
         if (timed && (e = (int)hipEventRecord(ctx->t0[v], st)) != 0) return e;
         hipStream_t vs = branch && v == cfsim::kBucketGlobal ? ctx->side : st;
-        if ((e = cfsim::launch_pair_lds(v, dtype, job, grid, vs)) != 0) return e;
+        if ((e = cfsim::launch_pair_lds(v, dtype, job, grid, vs, whole_cu)) != 0) return e;
         if (timed && (e = (int)hipEventRecord(ctx->t1[v], st)) != 0) return e;
     }
     if (branch) {

@@ -179,12 +179,13 @@ __host__ __device__ inline size_t lds_pair_bytes(const PairShape& s, int nnzR, i
 // workspace slot of `slot_elems` elements each; lists in LDS.
 constexpr int kGlobalThreads = 512;
 constexpr int kGlobalLds = 78 * 1024;  // bound of a pair's lists
+constexpr int kCuLds = 159 * 1024;     // leaves no room for a second such workgroup
 // The plain measure's global kernel: in FP32 a whole CU per pair, on strips
 // (strips.h); in FP64 gathers from S, two workgroups per CU (on strips the
 // FP64 row sums have no matrix instruction: 34.4 against 25.0 ms for the
 // all-pairs batch of 96 graphs).
 __host__ __device__ constexpr int plain_global_threads(int esize) { return esize == 8 ? kGlobalThreads : 1024; }
-__host__ __device__ constexpr int plain_global_lds(int esize) { return esize == 8 ? kGlobalLds : 159 * 1024; }
+__host__ __device__ constexpr int plain_global_lds(int esize) { return esize == 8 ? kGlobalLds : kCuLds; }
 
 // Orientation that fills 64-lane chunks better (ties keep S as n_B x n_A).
 __host__ __device__ inline int preferred_swap(int nA, int nB) {
@@ -354,7 +355,8 @@ struct PlanJob {
 // Host-side launchers (return hipError_t as int).
 // variant in [0, kNumVariants): LDS kernel; kBucketGlobal: global-memory
 // kernel; kBucketInvalid: marks the bucket's pairs invalid.
-int launch_pair_lds(int variant, int dtype, const PairJob& job, int grid, hipStream_t stream);
+// whole_cu: with a CU's whole LDS, so that no two of its workgroups share one.
+int launch_pair_lds(int variant, int dtype, const PairJob& job, int grid, hipStream_t stream, bool whole_cu = false);
 int launch_plan(const PlanJob& job, hipStream_t stream);
 int launch_buckets(const PlanJob& job, int32_t* bucket, hipStream_t stream);  // bucket of every pair
 const char* bucket_kernel_name(int bucket, int dtype);

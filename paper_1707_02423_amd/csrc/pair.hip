@@ -145,7 +145,7 @@ int lds_of(int v, int esize, int mode) {
 
 }  // namespace
 
-int launch_pair_lds(int variant, int dtype, const PairJob& job, int grid, hipStream_t stream) {
+int launch_pair_lds(int variant, int dtype, const PairJob& job, int grid, hipStream_t stream, bool whole_cu) {
     if (variant == kBucketInvalid) {
         hipLaunchKernelGGL(invalid_kernel, dim3(64), dim3(256), 0, stream, job);
         return (int)hipGetLastError();
@@ -155,7 +155,7 @@ int launch_pair_lds(int variant, int dtype, const PairJob& job, int grid, hipStr
     const int mode = job.damped ? kModeDamped : (job.resize ? kModeResized : kModePlain);
     return (int)hipLaunchKernel(variant_kernel(variant, dtype, mode), dim3(grid),
                                 dim3(threads_of(variant, esize, mode)), args,
-                                (size_t)lds_of(variant, esize, mode), stream);
+                                (size_t)(whole_cu ? kCuLds : lds_of(variant, esize, mode)), stream);
 }
 
 int launch_plan(const PlanJob& job, hipStream_t stream) {
@@ -187,9 +187,11 @@ int set_kernel_attributes() {
     for (int v = 0; v <= kBucketGlobal; ++v)
         for (int mode = kModePlain; mode <= kModeResized; ++mode) {
             e |= (int)hipFuncSetAttribute(variant_kernel(v, CFSIM_F32, mode),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds_of(v, 4, mode));
+                                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          v == kBucketGlobal ? kCuLds : lds_of(v, 4, mode));
             e |= (int)hipFuncSetAttribute(variant_kernel(v, CFSIM_F64, mode),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds_of(v, 8, mode));
+                                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          v == kBucketGlobal ? kCuLds : lds_of(v, 8, mode));
         }
     return e;
 }

@@ -59,3 +59,23 @@ def test_a_single_pairs_launches(cfm, ctx, dtype):
     assert _score_launches(cfm, ctx, 150, 160, dtype, 2000, 1e-2) == 1    # one workgroup
     e = 8 if dtype == "f64" else 4
     assert _score_launches(cfm, ctx, 150, 160, dtype, 200, 1e-12, ws_bytes=2 * 150 * 160 * e + 256) == 1
+
+
+@pytest.mark.parametrize("kw", [dict(dtype="f64"), dict(dtype="f32"), dict(dtype="f64", path="damped", alpha=0.85),
+                                dict(dtype="f32", path="damped", alpha=0.85)])
+def test_few_pairs_past_lds_score_as_among_many(cfm, ctx, kw):
+    # up to one pair per CU each has a CU's LDS to itself; the kernel and its
+    # results are the same
+    graphs = [make_cfg(n, Grammar(counts="trip"), seed=n) for n in (150, 163, 201, 149)]
+    gs = cfm.pack(ctx, graphs)
+    a, b = np.triu_indices(4)
+    a, b = a.astype(np.int32), b.astype(np.int32)
+    out = []
+    for times in (1, 30):   # 10 and 300 pairs
+        B = cfm.Batch(ctx, gs, np.tile(a, times), np.tile(b, times), max_iter=12, tol=0.0, want_S=True, **kw)
+        assert (B.buckets() == 5).all()
+        B.run()
+        torch.cuda.synchronize()
+        out.append((B.results()[:10].tobytes(), [m.tobytes() for m in B.matches()[:10]],
+                    [x.tobytes() for x in B.S_list()[:10]]))
+    assert out[0] == out[1]
