@@ -1447,6 +1447,14 @@ __device__ __forceinline__ bool greedy_bests(int nR, int nC, bool swp, const T* 
 // The same with S in global memory: wave w keeps the bests of the columns of
 // chunk w over all rows, two levels deep: per lane and segment of rows (in
 // LDS) and per lane.  A taken row costs its segment's rescan.
+// FP64 rows of up to 192 entries go to the sorted lists: 276 plain pairs of 115
+// nodes 652 us with them (2 updates), 757 here; 130: 1,028 / 1,083; 175: 1,592 /
+// 1,712; but 200: 2,081 / 2,119, 230: 2,640 / 2,577, 250: 2,981 / 2,872, 262:
+// 6,529 / 3,398 (by rounds there).  Damped and resized ones alike (130 damped
+// 1,086 / 1,130, resized 1,871 / 2,144).  FP32 is faster here at every size
+// (plain, 150: 1,403 / 1,304; damped 1,114 / 940, 230: 2,338 / 2,350), resized
+// the same (130: 1,793 / 1,800).
+constexpr int kSortedColsF64 = 192;
 template <typename T>
 __device__ __forceinline__ size_t best_segments_bytes(int nC, int segs) {
     return (size_t)segs * ((nC + kWave - 1) / kWave * kWave) * sizeof(Cand<T>);
@@ -1556,12 +1564,6 @@ __device__ __noinline__ bool greedy_in_lds(int nR, int nC, int swp, const T* S, 
     if (nC <= 2 * kWave) return greedy_bests<T, NT, 2>(nR, nC, swp != 0, S, rstate, cstate, red);
     return greedy_bests<T, NT, 4>(nR, nC, swp != 0, S, rstate, cstate, red);
 }
-template <typename T, int NT>
-__device__ __noinline__ bool greedy_in_memory(int nR, int nC, int swp, const T* S, int* rstate, int* cstate,
-                                              void* room, size_t room_bytes, double* red) {
-    return greedy_segments<T, NT>(nR, nC, swp != 0, S, rstate, cstate, room, room_bytes, red);
-}
-
 // Kept out of line: runs once per pair, and inlined it constrains the
 // register allocation of the update loop in the same kernel.  Its arguments
 // are scalars: a shape or list record passed by reference would have to live
@@ -1736,6 +1738,33 @@ __device__ __forceinline__ void greedy_rounds(const PairShape& sh, const T* S, T
 
 }
 
+// Step a7 with S in global memory, out of line as the others are.
+template <typename T, int NT>
+__device__ __noinline__ void match_in_memory(int nR, int nC, int swp, const T* S, T* St, int* rstate, int* rbest,
+                                             int* cstate, int* cbest, void* rec, int* s_count, double* red) {
+    // the lists up to rstate are free by now
+    const size_t room = (size_t)(reinterpret_cast<unsigned char*>(rstate) - static_cast<unsigned char*>(rec));
+    const bool sorted = sizeof(T) == 8 && nC <= kSortedColsF64;
+    if (!sorted && nC <= NT && best_segments_bytes<T>(nC, 4) <= room &&
+        greedy_segments<T, NT>(nR, nC, swp != 0, S, rstate, cstate, rec, room, red))
+        return;
+    if (nC <= kSortCols) {
+        greedy_sorted<T, NT>(nR, nC, swp, S, St, rstate, rbest, cstate, rec);
+    } else {
+        PairShape sh{};
+        sh.swap = swp;
+        sh.nR = nR;
+        sh.nC = nC;
+        Lists<T> G{};
+        G.rstate = rstate;
+        G.rbest = rbest;
+        G.cstate = cstate;
+        G.cbest = cbest;
+        G.rec = reinterpret_cast<RowRec<T>*>(rec);
+        greedy_rounds<T, NT>(sh, S, St, G, s_count);
+    }
+}
+
 // S (compute orientation, maybe transposed) to the n_B x n_A output.
 template <typename T, typename O, int NT>
 __device__ __forceinline__ void write_S(O* So, const T* S, long long total, int nA, int nC, bool swp) {
@@ -1763,22 +1792,20 @@ __device__ __forceinline__ void match_and_write(const PairJob& J, int p, const G
     int* rstate = G.rstate;
     int* cstate = G.cstate;
     // One wave alone walks sorted lists; a workgroup keeps cached bests, unless
-    // a wave would have more rows (LDS) or there are more column chunks than
-    // waves (global memory) than its state holds: then sorted lists or rounds.
-    const size_t room = (size_t)(reinterpret_cast<unsigned char*>(G.rstate) - reinterpret_cast<unsigned char*>(G.rec));
-    bool matched = false;
-    if constexpr (!GLOBAL) {
+    // a wave would have more rows than its state holds: then sorted lists or
+    // rounds.
+    if constexpr (GLOBAL) {
+        match_in_memory<T, NT>(sh.nR, nC, sh.swap, S, St, G.rstate, G.rbest, G.cstate, G.cbest, G.rec, s_count, red);
+    } else {
+        bool matched = false;
         if (NT > kWave && nC <= kSortCols && sh.nR <= 64 * NW)
             matched = greedy_in_lds<T, NT>(sh.nR, nC, sh.swap, S, G.rstate, G.cstate, red);
-    } else {
-        if (nC <= NW * kWave && best_segments_bytes<T>(nC, 4) <= room)
-            matched = greedy_in_memory<T, NT>(sh.nR, nC, sh.swap, S, G.rstate, G.cstate, G.rec, room, red);
+        if (matched) {
+        } else if (nC <= kSortCols)
+            greedy_sorted<T, NT>(sh.nR, nC, sh.swap, S, St, G.rstate, G.rbest, G.cstate, G.rec);
+        else
+            greedy_rounds<T, NT>(sh, S, St, G, s_count);
     }
-    if (matched) {
-    } else if (nC <= kSortCols)
-        greedy_sorted<T, NT>(sh.nR, nC, sh.swap, S, St, G.rstate, G.rbest, G.cstate, G.rec);
-    else
-        greedy_rounds<T, NT>(sh, S, St, G, s_count);
     // the row records and column infos are free now: they hold the picks
     const double margin = greedy_margin<T, NT>(S, sh.nR, nC, swp, rstate, cstate, reinterpret_cast<T*>(G.rec),
                                                reinterpret_cast<T*>(G.cinfo), red);
