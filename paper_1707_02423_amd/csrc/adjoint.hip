@@ -296,7 +296,8 @@ int launch_backward(int dtype, const SetRef& set, const int32_t* pair_a, const i
                     const cfsim_pair_result* fwd, const int32_t* match, const int64_t* match_off,
                     const double* grad_score, double* grad_w, int32_t* pair_status, int ckpt,
                     const void* fck, const int64_t* fck_off, int max_iter,
-                    void* ws, size_t ws_bytes, int max_nodes, long long slot_elems, int grid, hipStream_t stream) {
+                    void* ws, size_t ws_bytes, int max_nodes, long long slot_elems, int grid, bool strips,
+                    hipStream_t stream) {
     BwdJob J;
     J.set = set;
     J.pair_a = pair_a;
@@ -317,11 +318,16 @@ int launch_backward(int dtype, const SetRef& set, const int32_t* pair_a, const i
     J.slot_bytes = backward_slot_bytes(max_iter, ckpt, slot_elems, esize);
     // the strips path where it fits the workspace of the other: the size does
     // not depend on the route
-    const size_t strip_ws = fck ? bwd_strips_bytes(max_nodes, n_pairs, grid, ckpt, esize) : 0;
-    J.strip_nodes = strip_ws != 0 && ws_bytes >= strip_ws ? max_nodes : 0;
-    J.ws = ws;
+    J.strip_nodes = 0;
+    BwdJob S = J;
+    S.ckpt = ckpt < max_iter ? ckpt : max_iter;  // one segment at most: the launches of a shorter one
+    const size_t strip_ws = strips && fck ? bwd_strips_bytes(max_nodes, n_pairs, S.ckpt, esize) : 0;
     int e = 0;
-    if (J.strip_nodes && (e = launch_bwd_strips(dtype, J, max_nodes, grid / 2, stream)) != 0) return e;
+    if (strip_ws != 0 && ws_bytes >= strip_ws) {
+        J.strip_nodes = S.strip_nodes = max_nodes;
+        S.ws = ws;
+        if ((e = launch_bwd_strips(dtype, S, max_nodes, grid / 2, stream)) != 0) return e;
+    }
     // queue counter in front of the slots
     J.queue = static_cast<int32_t*>(ws);
     J.ws = static_cast<unsigned char*>(ws) + 256;

@@ -38,15 +38,18 @@ struct BwdShape {
     size_t lists, scratch_off;
     bool fits, lane_edges;
 };
-__device__ inline BwdShape bwd_shape(const GraphRef& A, const GraphRef& B, int esize) {
+// kept: A's edges after invalid ones were dropped (at most nnzA).
+__host__ __device__ inline BwdShape bwd_shape(int nA, int nB, int nnzA, int nnzB, int kept, int esize) {
     BwdShape s;
-    s.lists = lds_lists_bytes(B.n, A.n, B.nnz, A.nnz, esize);
-    s.scratch_off = s.lists + align16((size_t)(A.nnz + B.nnz) * 8) + align16((size_t)(A.nnz + B.nnz) * 4);
+    s.lists = lds_lists_bytes(nB, nA, nnzB, nnzA, esize);
+    s.scratch_off = s.lists + align16((size_t)(nnzA + nnzB) * 8) + align16((size_t)(nnzA + nnzB) * 4);
     s.fits = s.scratch_off <= (size_t)kBwdLds;
-    const int kept = A.rp[A.n];
     s.lane_edges = kept <= kAChunks * kWave &&
                    s.scratch_off + (size_t)kEdgeWaves * kAChunks * kWave * esize <= (size_t)kBwdLds;
     return s;
+}
+__device__ inline BwdShape bwd_shape(const GraphRef& A, const GraphRef& B, int esize) {
+    return bwd_shape(A.n, B.n, A.nnz, B.nnz, A.rp[A.n], esize);
 }
 
 // A pair of the call that can run (graphs and forward result).
@@ -70,8 +73,7 @@ __device__ inline bool bwd_on_strips(const BwdJob& J, const GraphRef& A, const G
     return s.fits && s.lane_edges && B.n <= J.strip_nodes && A.n <= J.strip_nodes;
 }
 
-// Host side of adjoint_strips.hip (bwd_strips_bytes is its workspace; 0: the path
-// does not take such a call).
+// Host side of adjoint_strips.hip.
 int launch_bwd_strips(int dtype, const BwdJob& J, int max_nodes, int num_cus, hipStream_t stream);
 
 }  // namespace cfsim

@@ -784,16 +784,7 @@ int run(const BwdJob& J, int max_nodes, int num_cus, hipStream_t stream) {
 
 }  // namespace
 
-// Up to one pair per CU (the one-workgroup kernel then leaves CUs idle or waits
-// for its largest pair), of at least 32 nodes at most.  Backward of 200 updates,
-// one workgroup per pair against this path (ms): 2 FP32 pairs of 256 nodes 53.2 /
-// 6.2; 160 of 16-256 43.4 / 12.9; 256 of 120-128 26.4 / 15.7; 256 of 60-64 8.5 /
-// 6.4; 64 of 8-48 3.1 / 1.9; but 512 of 120-128 31.8 / 35.2, 512 of 8-64 5.9 /
-// 6.4 and one of 12 x 16 1.2 / 1.6 (two hundred launches).
-size_t bwd_strips_bytes(int max_nodes, long long n_pairs, int grid, int ckpt, int esize) {
-    const int num_cus = grid / 2;
-    if (max_nodes < 32 || max_nodes > kBwdStripNodes || n_pairs < 1 || n_pairs > num_cus || n_pairs > kMaxPairs)
-        return 0;
+size_t bwd_strips_bytes(int max_nodes, long long n_pairs, int ckpt, int esize) {
     const long long elems = (long long)max_nodes * max_nodes;
     const AdjLayout l = esize == 8 ? layout_of<double>(max_nodes, elems, ckpt) : layout_of<float>(max_nodes, elems, ckpt);
     return header_bytes((int)n_pairs, l.max_strips) + (size_t)n_pairs * l.total;
@@ -804,3 +795,38 @@ int launch_bwd_strips(int dtype, const BwdJob& J, int max_nodes, int num_cus, hi
 }
 
 }  // namespace cfsim
+
+// Calls that have the forward's checkpoints run on strips
+//   - up to one pair per CU (the one-workgroup kernel then leaves CUs idle or
+//     waits for its largest pair), in FP64 up to one per two CUs, of 32 nodes or
+//     more.  Backward of 200 updates, one workgroup per pair against strips (ms):
+//     FP32, 2 pairs of 250-256 nodes 54.5 / 6.2; 160 of 16-256 82.2 / 19.4; 100 of
+//     90-128 17.3 / 6.5, 250 of them 22.7 / 13.2; 100 of 60-64 7.7 / 3.5, 250
+//     8.6 / 6.2; 64 of 8-48 3.3 / 2.0; but 512 of 120-128 31.8 / 35.2, 512 of
+//     8-64 5.9 / 6.4 and one of 12 x 16 1.2 / 1.6.  FP64, 100 of 90-128 22.5 /
+//     12.5, 100 of 60-64 8.7 / 5.9, 64 of 8-48 3.6 / 3.3, but 250 of 90-128 29.9 /
+//     32.3 and of 60-64 10.2 / 12.8.
+//   - where the set's largest pairs are strips' pairs: else the one-workgroup
+//     kernel, which takes those after the strips, sets the time alone (FP64, 160
+//     pairs of 16-256: 163 / 203).
+//   - where the updates to expect pay for the launches, 4.2 us each and as many
+//     as max_iter asks for whenever the pairs stopped, against a saving that
+//     grows with the pair, about n^2 / 400 us per update (FP64 n^2 / 1000; FP32
+//     3 to 7 us for 40-48 nodes, 10-22 for 64, 47-55 for 128, 240 for 256; FP64 2
+//     for 40-48, 10-15 for 64, 48 for 128): two FP32 pairs of 250-256 nodes that
+//     stopped after two updates of max_iter 2000 take 0.7 ms in one workgroup each
+//     and 8.9 on strips.
+extern "C" int cfsim_route_backward_strips(const cfsim_graph_set* set, int64_t n_pairs, const cfsim_options* opt,
+                                           int32_t checkpoint_every, int32_t num_cus) {
+    using namespace cfsim;
+    const bool f64 = opt->dtype == CFSIM_F64;
+    const int n = set->max_nodes;
+    if (n < 32 || n > kBwdStripNodes) return 0;
+    if (n_pairs < 1 || n_pairs > (f64 ? num_cus / 2 : num_cus) || n_pairs > kMaxPairs) return 0;
+    const int nnz = mean_jumps(set, n);
+    const BwdShape s = bwd_shape(n, n, nnz, nnz, nnz, f64 ? 8 : 4);
+    if (!s.fits || !s.lane_edges) return 0;
+    const double every = checkpoint_every < opt->max_iter ? checkpoint_every : opt->max_iter;
+    const double launches = (ceil(opt->max_iter / every) + 1.0) * (every + 1.0) + 5.0;
+    return 4.2 * launches <= updates_expected(opt) * (n * (double)n / (f64 ? 1000.0 : 400.0) + 4.2 * (1.0 + 1.0 / every));
+}

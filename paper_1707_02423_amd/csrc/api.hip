@@ -430,6 +430,21 @@ cfsim_status check_large_limits(int max_nodes, const cfsim_options* opt) {
 
 }  // namespace
 
+// Updates to expect before a tolerance stops a pair: of 120 pairs of generated
+// control-flow graphs (8 to 410 nodes) nine in ten made at least 52 at tol 1e-3,
+// 70 at 1e-4, 128 at 1e-6, 350 at 1e-9 and 425 at 1e-12 (the first one of all
+// stopped after 44, 58, 86, 130 and 176): 17 per decade and more.  tol = 0 never
+// stops one.
+double cfsim::updates_expected(const cfsim_options* opt) {
+    const double k = opt->tol > 0.0 ? std::fmax(0.0, -17.0 * std::log10(opt->tol)) : opt->max_iter;
+    return std::fmin(k, opt->max_iter);
+}
+
+int cfsim::mean_jumps(const cfsim_graph_set* set, int n) {
+    const double jumps = (double)set->total_edges / (double)(set->total_nodes > 0 ? set->total_nodes : 1);
+    return (int)std::fmin(std::ceil(jumps * n), 1e8);
+}
+
 extern "C" {
 
 const char* cfsim_last_error(void) { return g_err.c_str(); }
@@ -609,16 +624,6 @@ static int plain_variant(int nA, int nB, int nnzA, int nnzB, int esize, cfsim::P
     return first;
 }
 
-// Updates to expect before a tolerance stops a pair: of 120 pairs of generated
-// control-flow graphs (8 to 410 nodes) nine in ten made at least 52 at tol 1e-3,
-// 70 at 1e-4, 128 at 1e-6, 350 at 1e-9 and 425 at 1e-12 (the first one of all
-// stopped after 44, 58, 86, 130 and 176): 17 per decade and more.  tol = 0 never
-// stops one.
-static double updates_expected(const cfsim_options* opt) {
-    const double k = opt->tol > 0.0 ? std::fmax(0.0, -17.0 * std::log10(opt->tol)) : opt->max_iter;
-    return std::fmin(k, opt->max_iter);
-}
-
 // Whether a plain pair past LDS runs on strips.  Their launches are enqueued
 // for max_iter updates whenever the pair stops, and an empty one takes 4.0 us,
 // where one workgroup ends with the pair but needs 1.05 ns (FP64 1.65) per entry
@@ -630,7 +635,7 @@ int cfsim_route_score_strips(int n_a, int n_b, const cfsim_options* opt) {
     const int largest = n_a > n_b ? n_a : n_b;
     if (largest > cfsim::kStripMaxNodes || opt->max_iter > cfsim::kStripMaxIter) return 0;
     const double saved_us = 0.9 * (opt->dtype == CFSIM_F64 ? 1.65e-3 : 1.05e-3) * (double)n_a * (double)n_b;
-    return 4.0 * opt->max_iter <= updates_expected(opt) * saved_us;
+    return 4.0 * opt->max_iter <= cfsim::updates_expected(opt) * saved_us;
 }
 
 static size_t score_ws_min(int32_t n_a, int32_t n_b, const cfsim_options* opt) {
@@ -831,8 +836,7 @@ struct Damping {
 // resized FP32 pairs of 8-150 nodes 21.5 ms in line, 16.5 with it.
 int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize) {
     const int n = set->max_nodes, esize = esize_of(dtype);
-    const double jumps = (double)set->total_edges / (double)(set->total_nodes > 0 ? set->total_nodes : 1);
-    const int nnz = (int)std::fmin(std::ceil(jumps * n), 1e8);
+    const int nnz = cfsim::mean_jumps(set, n);
     for (int v = 0; v < cfsim::kNumVariants; ++v) {
         cfsim::PairShape sh;
         if (resize ? cfsim::resized_fits(n, n, nnz, nnz, v, esize) : cfsim::choose_shape(n, n, nnz, nnz, v, esize, &sh))
@@ -1291,6 +1295,7 @@ cfsim_status cfsim_score_backward(cfsim_context* ctx, const cfsim_graph_set* set
     e = cfsim::launch_backward(opt->dtype, ref_of(set), pair_a, pair_b, (int)n_pairs, fwd, match, match_off,
                                grad_score, grad_w, pair_status, checkpoint_every, ckpt, ckpt_off, opt->max_iter, ws, need,
                                set->max_nodes, global_slot_elems(set->max_nodes), cfsim::backward_grid(ctx->num_cus),
+                               cfsim_route_backward_strips(set, n_pairs, opt, checkpoint_every, ctx->num_cus) != 0,
                                static_cast<hipStream_t>(stream));
     if (e != 0) return hip_fail(e, "backward launch");
     return ok();

@@ -480,9 +480,9 @@ int launch_backward(int dtype, const SetRef& set, const int32_t* pair_a, const i
                     const cfsim_pair_result* fwd, const int32_t* match, const int64_t* match_off,
                     const double* grad_score, double* grad_w, int32_t* pair_status, int ckpt,
                     const void* fck, const int64_t* fck_off, int max_iter,
-                    void* ws, size_t ws_bytes, int max_nodes, long long slot_elems, int grid,
+                    void* ws, size_t ws_bytes, int max_nodes, long long slot_elems, int grid, bool strips,
                     hipStream_t stream);
-size_t bwd_strips_bytes(int max_nodes, long long n_pairs, int grid, int ckpt, int esize);
+size_t bwd_strips_bytes(int max_nodes, long long n_pairs, int ckpt, int esize);  // workspace of the strips path
 
 // Top-k (topk.hip).
 long long topk_blocks(long long n);
@@ -525,11 +525,18 @@ int launch_assign(int dtype, const void* S, const int64_t* S_off, const int32_t*
 constexpr int kWardMaxObs = 4096;
 int launch_ward(const double* X, int n, int f, double* Z, double* D, hipStream_t stream);
 
+// For the rules that choose a route: jumps of an n-node graph at the set's mean
+// density, and the updates to expect before opt's tolerance stops a pair (api.hip).
+int mean_jumps(const cfsim_graph_set* set, int n);
+double updates_expected(const cfsim_options* opt);
+
 }  // namespace cfsim
 
-// Host rules that choose between the routes of a call (api.hip).  They are no
+// Host rules that choose between the routes of a call.  They are no
 // part of the ABI of cfsim.h; C linkage so that tests can ask them without a GPU.
 extern "C" {
 int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize);
 int cfsim_route_score_strips(int n_a, int n_b, const cfsim_options* opt);
+int cfsim_route_backward_strips(const cfsim_graph_set* set, int64_t n_pairs, const cfsim_options* opt,
+                                int32_t checkpoint_every, int32_t num_cus);
 }

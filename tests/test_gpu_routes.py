@@ -79,3 +79,35 @@ def test_few_pairs_past_lds_score_as_among_many(cfm, ctx, kw):
         out.append((B.results()[:10].tobytes(), [m.tobytes() for m in B.matches()[:10]],
                     [x.tobytes() for x in B.S_list()[:10]]))
     assert out[0] == out[1]
+
+
+def _backward_launches(cfm, ctx, sizes, pairs, dtype, max_iter, tol, every):
+    gs = cfm.pack(ctx, [make_cfg(n, Grammar(counts="trip"), seed=q) for q, n in enumerate(sizes)])
+    a = np.arange(pairs, dtype=np.int32) % len(sizes)
+    B = cfm.Batch(ctx, gs, a, a[::-1].copy(), dtype=dtype, max_iter=max_iter, tol=tol, checkpoint_every=every)
+    B.run()
+    L = cfm.lib()
+    size = L.cfsim_backward_workspace_size(ctx.handle, ctypes.byref(B.set_c), pairs, ctypes.byref(B.opt), every)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    one = torch.ones(pairs, dtype=torch.float64, device="cuda")
+    grad = torch.zeros(gs.total_edges, dtype=torch.float64, device="cuda")
+    return launches(cfm, lambda s: L.cfsim_score_backward(
+        ctx.handle, ctypes.byref(B.set_c), B.pair_a.data_ptr(), B.pair_b.data_ptr(), pairs, ctypes.byref(B.opt),
+        B.res.data_ptr(), B.match.data_ptr(), B.match_off.data_ptr(), one.data_ptr(), grad.data_ptr(), None, every,
+        B.ckpt.data_ptr(), B.ckpt_off.data_ptr(), ws.data_ptr(), size, s))
+
+
+ONE_WORKGROUP = 2   # the queue's counter and the kernel
+
+
+def test_the_reverses_launches(cfm, ctx):
+    def n(*a):
+        return _backward_launches(cfm, ctx, *a)
+    # strips: (rounds + 1) of a segment's launches, a seam before the first and between rounds
+    assert n([128, 100, 60], 3, "f32", 40, 0.0, 8) == 3 + 6 * 8 + 6 + ONE_WORKGROUP
+    assert n([128, 100, 60], 3, "f64", 40, 0.0, 8) == 3 + 6 * 8 + 6 + ONE_WORKGROUP
+    assert n([128, 100, 60], 3, "f32", 40, 0.0, 1000) == 3 + 2 * 40 + 2 + ONE_WORKGROUP  # a segment as long as the call
+    # one workgroup per pair: stopped early, too many in FP64, pairs that are no strips' pairs
+    assert n([128, 100, 60], 3, "f32", 2000, 0.5, 8) == ONE_WORKGROUP
+    assert n([64, 50, 60], 130, "f64", 16, 0.0, 4) == ONE_WORKGROUP
+    assert n([400, 420], 2, "f32", 16, 0.0, 4) == ONE_WORKGROUP

@@ -54,3 +54,22 @@ def test_the_workspace_of_a_pair_is_that_of_its_route(dtype, n_a, n_b, kw, buffe
     # strips keep lists of 56 (FP64: 96) bytes per column and tables of 496 (1,152) per four rows beside their iterates
     lists = 200 * (n_a + n_b + 64) * (2 if dtype == "f64" else 1)
     assert buffers * one <= size <= buffers * one + (lists if buffers == 4 else 256)
+
+
+@pytest.mark.parametrize("dtype,max_nodes,pairs,max_iter,tol,every,strips", [
+    ("f32", 256, 160, 200, 1e-12, 8, 1), ("f32", 256, 256, 200, 1e-12, 8, 1), ("f32", 32, 1, 200, 1e-12, 8, 1),
+    ("f64", 128, 128, 200, 1e-12, 8, 1), ("f32", 128, 100, 200, 1e-3, 8, 1), ("f32", 256, 4, 1000, 0.0, 8, 1),
+    # more pairs than the strips gain from, and sizes below and past them
+    ("f32", 256, 257, 200, 1e-12, 8, 0), ("f64", 128, 129, 200, 1e-12, 8, 0), ("f32", 31, 1, 200, 1e-12, 8, 0),
+    ("f64", 256, 100, 200, 1e-12, 8, 0), ("f32", 512, 16, 200, 1e-12, 8, 0), ("f32", 513, 1, 200, 1e-12, 8, 0),
+    # stopped early, or too few updates
+    ("f32", 256, 2, 2000, 1e-2, 8, 0), ("f32", 64, 100, 200, 1e-2, 8, 0), ("f64", 128, 10, 4000, 1e-4, 8, 0),
+    ("f32", 40, 1, 2, 0.0, 8, 0), ("f32", 128, 1, 200, 1.0, 8, 0),
+    # a segment longer than the call has no launches of its own
+    ("f32", 128, 10, 200, 1e-12, 100000, 1),
+])
+def test_the_reverse_takes_strips_where_they_pay(dtype, max_nodes, pairs, max_iter, tol, every, strips):
+    s = _set(max_nodes)
+    opt = cf.options(dtype, max_iter, tol)
+    L = cf.lib()
+    assert L.cfsim_route_backward_strips(ctypes.byref(s), ctypes.c_int64(pairs), ctypes.byref(opt), every, 256) == strips
