@@ -100,13 +100,17 @@ def cpu_baseline(n_pairs_total: int, sample: int, seed: int = 7, gpu_S=None):
     return out
 
 
+PAIR_SOURCES = ("cfsim_internal.h", "pair_device.h", "strips.h", "pair_kernels.h", "pair.hip",
+                "pair_plain_f32.hip", "pair_plain_f64.hip")
+
+
 def kernel_sources_digest() -> str:
     """SHA-256 over the sources the batched pair kernels are built from
     (detects kernels changed since their counters were taken)."""
     import hashlib
     d = os.path.join(ROOT, "paper_1707_02423_amd", "csrc")
     h = hashlib.sha256()
-    for name in ("cfsim_internal.h", "pair_device.h", "pair_kernels.h", "pair.hip"):
+    for name in PAIR_SOURCES:
         with open(os.path.join(d, name), "rb") as f:
             h.update(name.encode() + b"\0" + f.read())
     return h.hexdigest()
