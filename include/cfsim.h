@@ -205,10 +205,18 @@ cfsim_status cfsim_pack(cfsim_context* ctx, int32_t n_graphs, int64_t total_node
                         void* ws, size_t ws_bytes, void* stream);
 
 /*
- * Steps a2-a7 for one pair (plain path, one launch): S_out (n_B x n_A
+ * Steps a2-a7 for one pair (plain path): S_out (n_B x n_A
  * row-major, opt->dtype; or n_M x n_M, n_M = max(n_A, n_B), when resized),
  * match_out[n_B] (or [n_M]) and res[1] are device memory; S_out and
- * match_out may be NULL.  With opt->resize = CFSIM_RESIZE_BILINEAR
+ * match_out may be NULL.  A pair that fits a workgroup's LDS is one launch
+ * (two with CFSIM_FLAG_FP64_FINAL).  A larger one of at most 1024 nodes per graph
+ * runs over the whole chip in up to opt->max_iter + 8 launches, all of them
+ * enqueued whenever the pair converges, if the updates to expect pay for them
+ * (max_iter at most 4096; tol = 0, or a tol that lets expect enough of max_iter)
+ * and ws holds cfsim_score_workspace_size() bytes; with less, down to two
+ * iterates (2 n_A n_B elements, of FP64 with CFSIM_FLAG_FP64_FINAL), or else
+ * in one launch of one workgroup.  The two differ in the last bits of S, by the
+ * order of the norm sums.  With opt->resize = CFSIM_RESIZE_BILINEAR
  * (Section 4 and Section 4.1: the smaller transition matrix X becomes
  * R X R^T with the order-1 interpolation R from its m nodes to n_M points
  * at p (m - 1) / (n_M - 1)) a pair of unequal sizes runs in the resized
@@ -227,8 +235,11 @@ cfsim_status cfsim_score(cfsim_context* ctx, const cfsim_graph* A, const cfsim_g
  * cfsim_score without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc).  Same arguments (minus ws,
- * ws_bytes), kernels, outputs and per-pair semantics as cfsim_score; the
- * workspace is a static device array of CFSIM_NOALLOC_SCRATCH_BYTES that
+ * ws_bytes), outputs and per-pair semantics as cfsim_score, and the kernels that
+ * it takes with a workspace of CFSIM_NOALLOC_SCRATCH_BYTES: a pair whose
+ * cfsim_score_workspace_size is larger (FP32 beyond about 1,000 x 1,000 nodes,
+ * FP64 beyond about 700 x 700, where its lists fit the kernels at all) runs in
+ * one workgroup.  The workspace is a static device array of that size, which
  * each GPU holds until the process ends (its address is taken once per
  * device by cfsim_context_create).  The call allocates nothing: a pair whose
  * two iterates (resized: cfsim_score_workspace_size) exceed
@@ -356,6 +367,9 @@ cfsim_status cfsim_context_get_tune(const cfsim_context* ctx, int32_t dtype, int
  * ckpt / ckpt_off are given (from cfsim_score_batch_ckpt with the same
  * checkpoint_every; both NULL: the forward is recomputed here first, S stored
  * every checkpoint_every updates).
+ * With checkpoints and few pairs the call may enqueue a launch per update and
+ * segment, up to about max_iter (1 + 1 / checkpoint_every) + 2 checkpoint_every,
+ * whatever fwd[p].iters says; else it is two launches.
  * Degenerate pairs contribute zero.  pair_status[n_pairs] (device, may be
  * NULL) receives 0, or CFSIM_INVALID_INPUT for a pair that was skipped (bad
  * ids, or lists too long for the kernel).  Graphs shared between pairs

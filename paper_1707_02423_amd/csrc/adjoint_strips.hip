@@ -800,7 +800,7 @@ int launch_bwd_strips(int dtype, const BwdJob& J, int max_nodes, int num_cus, hi
 //   - up to one pair per CU (the one-workgroup kernel then leaves CUs idle or
 //     waits for its largest pair), in FP64 up to one per two CUs, of 32 nodes or
 //     more.  Backward of 200 updates, one workgroup per pair against strips (ms):
-//     FP32, 2 pairs of 250-256 nodes 54.5 / 6.2; 160 of 16-256 82.2 / 19.4; 100 of
+//     FP32, 2 pairs of 250-256 nodes 54.5 / 6.2; 160 of 16-256 paired by size 82.2 / 19.4; 100 of
 //     90-128 17.3 / 6.5, 250 of them 22.7 / 13.2; 100 of 60-64 7.7 / 3.5, 250
 //     8.6 / 6.2; 64 of 8-48 3.3 / 2.0; but 512 of 120-128 31.8 / 35.2, 512 of
 //     8-64 5.9 / 6.4 and one of 12 x 16 1.2 / 1.6.  FP64, 100 of 90-128 22.5 /

@@ -541,10 +541,13 @@ __global__ __launch_bounds__(kStepThreads) void large_step(LargeJob J, int k) {
 // entry are added in the order of large_step's gathers: the same bits.
 //
 // Bound by the latency of a strip's two stages with two workgroups per CU
-// (64 KB of LDS for 2,048 columns): 70 us per launch for 8 FP32 pairs of
+// (64 KB of LDS for 2,048 columns): 65 us per launch for 8 FP32 pairs of
 // 512-2048 nodes, against 165 us on the gathers of large_step.  With 1,024
-// threads (64 registers per lane) the column loop spills: 254 us; with the
-// long rows' call inside the loop 118 us.
+// threads 78 us (one workgroup per CU, 64 registers per lane); with the long
+// rows' call inside the loop 118 us.  FP64, whose row sums have no matrix
+// instruction, gains too (whole calls of 42 updates, gathers against strips, ms):
+// 8 pairs of 512-2048 nodes 23.4 / 17.6, 8 of 512-1024 9.7 / 5.7, 32 of 150-250
+// 4.4 / 2.9, 100 of 60-128 4.1 / 3.0, 200 of 8-40 2.4 / 1.4.
 constexpr int kStripDP = kLP;
 
 template <typename T>

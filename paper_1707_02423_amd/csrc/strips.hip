@@ -3,11 +3,16 @@
 // pair runs on as many CUs as it has strips instead of on one.  A launch reads
 // the norm partials the previous one left and takes the stopping decision
 // itself, the same in every workgroup, so an update is one launch without a
-// reduction between.  The results are those of the one-workgroup kernel.
+// reduction between.  The terms of an entry are added in the order of the
+// one-workgroup kernel; the norms' partial sums are grouped by strips and 1 / nu
+// is rounded twice here, so that S agrees up to the rounding of the scale.
 //
 // Bound by the latency of one launch: its start, three dependent reads from
 // memory and the barrier between the two stages, 6.3 us per update for a
-// 333 x 410 FP32 pair (103 workgroups) against 170 us on one CU.  Such a pair is
+// 333 x 410 FP32 pair (103 workgroups) against 145 us on one CU; 13.9 us where one
+// node of the pair has more than four predecessors (the pass over such rows is
+// a serial chain of its own).  The launches follow max_iter, not the updates
+// done: cfsim_route_score_strips (api.hip) says where that pays.  Such a pair is
 // matched in 0.6 ms by the large path's kernels (lines sorted over the chip), in
 // 1.9 ms by one workgroup that keeps the columns' bests (which most columns
 // agree on, so that most of them are looked up again at every pick).
