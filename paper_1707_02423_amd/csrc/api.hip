@@ -918,15 +918,19 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
             job.gws = b.slots[v];
             job.slot_elems = resize ? cfsim::resized_slot_elems(set->max_nodes) : global_slot_elems(set->max_nodes);
             grid = ctx->grid[d][v];
-            // Up to one pair per CU: one workgroup per CU, which takes its whole
+            // Up to one pair per CU: one workgroup per pair, which takes a CU's whole
             // LDS.  Two that share a CU while others idle slow each other down, and
             // whether the dispatcher places them so depends on what ran before:
             // 190 FP64 pairs of 200 nodes 27.8 ms with two per CU, 23.1 with one
             // (23.4-25.7 behind the LDS kernels' launches, before the branch); 28
-            // damped FP32 ones 22.5-23.8 / 19.7.  Resized pairs, whose call has
-            // LDS and tiled pairs beside them: 28.6 with two, 30.5 with one.
+            // damped FP32 ones 22.5-23.8 / 19.7.  More workgroups than pairs would
+            // take the pairs in no even spread over the XCDs, and the LDS kernels
+            // beside the branch wait while one XCD has no CU left: training step of
+            // 160 pairs of 16-256 nodes 25.3 ms with 256 workgroups, 22.7 with 160.
+            // Resized pairs, whose call has LDS and tiled pairs beside them: 28.6 ms
+            // with two per CU, 30.5 with one.
             if (!resize && n_pairs <= num_cus_of(ctx)) {
-                grid = num_cus_of(ctx);
+                grid = (int)n_pairs;
                 whole_cu = true;
             } else if (resize || dm.on) {
                 grid = num_cus_of(ctx) * lds_blocks_per_cu(v, esize);
