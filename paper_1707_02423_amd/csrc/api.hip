@@ -25,7 +25,9 @@ struct cfsim_context {
     int num_cus = 0;
     int grid[2][cfsim::kBucketGlobal + 1] = {};  // persistent grid per [dtype][LDS variant | global]
     hipStream_t cap = nullptr;              // capture stream of the cached graphs
-    hipStream_t side = nullptr;             // its branch for the global-memory bucket
+    // its branch for the global-memory bucket, made by the first call that takes
+    // it (they cost 70 us to make and 400 us to destroy)
+    hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -487,12 +489,9 @@ cfsim_status cfsim_context_create(cfsim_context** out, int device) {
         delete ctx;
         return hip_fail(e, "hipGetSymbolAddress(scratch)");
     }
-    if ((e = (int)hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking)) != 0 ||
-        (e = (int)hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking)) != 0 ||
-        (e = (int)hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming)) != 0 ||
-        (e = (int)hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming)) != 0) {
-        cfsim_context_destroy(ctx);
-        return hip_fail(e, "capture streams");
+    if ((e = (int)hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking)) != 0) {
+        delete ctx;
+        return hip_fail(e, "hipStreamCreateWithFlags");
     }
     *out = ctx;
     return ok();
@@ -845,6 +844,19 @@ int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize) {
     return 1;
 }
 
+// The branch's stream and events for a call that may take it, before its capture.
+static int make_branch(cfsim_context* ctx, const cfsim_graph_set* set, const cfsim_options* opt) {
+    const int resize = opt->resize == CFSIM_RESIZE_BILINEAR;
+    if (ctx->join || !(cfsim_route_branch(set, opt->dtype, resize) ||
+                       (fp64_final(opt) && cfsim_route_branch(set, CFSIM_F64, resize))))
+        return 0;
+    int e = 0;
+    if (!ctx->side) e = (int)hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
+    if (e == 0 && !ctx->fork) e = (int)hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming);
+    if (e == 0) e = (int)hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming);
+    return e;
+}
+
 static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const int32_t* pair_a, const int32_t* pair_b,
                         int64_t n_pairs, const cfsim_options* opt, int dtype, const cfsim_pair_result* filter,
                         cfsim_pair_result* res, int32_t* match, const int64_t* match_off, void* S_out,
@@ -896,7 +908,7 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
     // largest pairs, often fewer than CUs; in a captured call it runs beside
     // the others on a branch of the graph, started first, unless the set has
     // no pair for it.
-    const bool branch = st == ctx->cap && !timed && cfsim_route_branch(set, dtype, resize);
+    const bool branch = st == ctx->cap && !timed && ctx->join && cfsim_route_branch(set, dtype, resize);
     if (branch) {
         if ((e = (int)hipEventRecord(ctx->fork, st)) != 0) return e;
         if ((e = (int)hipStreamWaitEvent(ctx->side, ctx->fork, 0)) != 0) return e;
@@ -1060,6 +1072,7 @@ static cfsim_status score_batch(cfsim_context* ctx, const cfsim_graph_set* set, 
             if (e != 0) return hip_fail(e, "resized batch launch");
             return ok();
         }
+        if ((e = make_branch(ctx, set, opt)) != 0) return hip_fail(e, "graph branch");
         auto key = set_call_key(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws);
         return replay_or_capture(ctx, &ctx->graph, &ctx->exec, &ctx->key, key, st, [&](hipStream_t cs) {
             return enqueue_resized(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws,
@@ -1073,6 +1086,7 @@ static cfsim_status score_batch(cfsim_context* ctx, const cfsim_graph_set* set, 
         if (ctx->timing) ctx->timed = 1;
         return ok();
     }
+    if ((e = make_branch(ctx, set, opt)) != 0) return hip_fail(e, "graph branch");
     auto key = set_call_key(ctx, set, pair_a, pair_b, n_pairs, opt, res, match, match_off, S_out, S_off, ws);
     append_key(key, ck.ptr);
     append_key(key, ck.off);
