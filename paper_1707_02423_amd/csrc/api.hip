@@ -825,23 +825,37 @@ struct Damping {
     const int64_t* prior_off;
 };
 
-// Whether a set can have pairs past a workgroup's LDS: no LDS kernel holds two
-// graphs of its largest size and mean number of jumps per node.  (Where the
-// mean misjudges a graph, its pairs run in line or the branch is empty.)  An
-// empty branch costs 15-20 us (3 pairs of 8-40 nodes at 2 updates: 176 us in
-// line, 197 with it), and in a resized call, whose 600 launches of the tiled
-// path each take longer in a graph that is no chain, 0.7 ms (91 FP32 pairs of
-// 7-76 nodes: 6.8 ms in line, 7.55 with it).  With such pairs it gains: 28
-// resized FP32 pairs of 8-150 nodes 21.5 ms in line, 16.5 with it.
-int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize) {
-    const int n = set->max_nodes, esize = esize_of(dtype);
+// Whether an LDS kernel holds two n-node graphs at the set's mean density.
+static bool lds_holds(const cfsim_graph_set* set, int n, int esize, int resize) {
     const int nnz = cfsim::mean_jumps(set, n);
     for (int v = 0; v < cfsim::kNumVariants; ++v) {
         cfsim::PairShape sh;
         if (resize ? cfsim::resized_fits(n, n, nnz, nnz, v, esize) : cfsim::choose_shape(n, n, nnz, nnz, v, esize, &sh))
-            return 0;
+            return true;
     }
-    return 1;
+    return false;
+}
+
+// Whether a set can have pairs past a workgroup's LDS and others beside them: no
+// LDS kernel holds two graphs of its largest size and mean number of jumps per
+// node, and not nearly every graph is of that size with the mean one past LDS
+// too.  (Where the mean misjudges a graph, its pairs run in line or the branch is
+// empty.)
+// An empty branch costs 15-20 us (3 pairs of 8-40 nodes at 2 updates: 176 us in
+// line, 197 with it), and in a resized call, whose 600 launches of the tiled
+// path each take longer in a graph that is no chain, 0.7 ms (91 FP32 pairs of
+// 7-76 nodes: 6.8 ms in line, 7.55 with it).  With pairs on both sides it gains:
+// 28 resized FP32 pairs of 8-150 nodes 21.5 ms in line, 16.5 with it.  Where all
+// are past LDS it gains nothing, and the kernel, which then starts on an idle
+// chip, has its workgroups placed less evenly (276 FP64 pairs of 126-134 nodes
+// 7.2 ms in line, 7.6 with it; damped FP32 ones of 150 nodes and four jumps per
+// node 126 / 138).  Resized sets branch all the same, since their pairs past LDS
+// need not be those of the largest sizes (276 pairs of 111-119 nodes 5.7 / 4.8).
+int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize) {
+    const int n = set->max_nodes, esize = esize_of(dtype);
+    if (lds_holds(set, n, esize, resize)) return 0;
+    const int mean = (int)(set->total_nodes / set->n_graphs);
+    return resize || mean < 0.9 * n || lds_holds(set, mean, esize, resize);
 }
 
 // The branch's stream and events for a call that may take it, before its capture.
@@ -906,16 +920,15 @@ static int enqueue_pass(cfsim_context* ctx, const cfsim_graph_set* set, const in
     // device: a bucket's persistent grid drains its queue longest pair first,
     // so its tail is about one pair long.  The global-memory bucket holds the
     // largest pairs, often fewer than CUs; in a captured call it runs beside
-    // the others on a branch of the graph, started first, unless the set has
-    // no pair for it.
+    // the others on a branch of the graph, started first, where
+    // cfsim_route_branch expects pairs on both sides; else behind them.
     const bool branch = st == ctx->cap && !timed && ctx->join && cfsim_route_branch(set, dtype, resize);
     if (branch) {
         if ((e = (int)hipEventRecord(ctx->fork, st)) != 0) return e;
         if ((e = (int)hipStreamWaitEvent(ctx->side, ctx->fork, 0)) != 0) return e;
     }
-    const int bucket_order[cfsim::kBuckets] = {cfsim::kBucketGlobal, 0, 1, 2, 3, 4, cfsim::kBucketInvalid};
-    static_assert(cfsim::kBucketGlobal == 5 && cfsim::kBuckets == 7, "bucket_order names every bucket");
-    for (const int v : bucket_order) {
+    for (int i = 0; i < cfsim::kBuckets; ++i) {
+        const int v = !branch || i > cfsim::kBucketGlobal ? i : (i + cfsim::kBucketGlobal) % (cfsim::kBucketGlobal + 1);
         if (filter && v == cfsim::kBucketInvalid) continue;  // the FP64 pass leaves no pair invalid
         job.bounds = b.bounds + 2 * v;
         job.queue = b.queues + v;

@@ -24,6 +24,16 @@ def test_a_batch_branches_only_for_pairs_past_lds(dtype, resize, max_nodes, jump
     assert cf.lib().cfsim_route_branch(ctypes.byref(s), d, resize) == branch
 
 
+@pytest.mark.parametrize("mean,most,resize,branch", [
+    (145, 150, 0, 0), (120, 150, 0, 1), (145, 150, 1, 1),
+    (130, 140, 0, 1),   # the mean pair is in LDS
+    (300, 400, 0, 1), (390, 400, 0, 0),
+])
+def test_a_batch_of_equal_sizes_past_lds_stays_one_chain(mean, most, resize, branch):
+    s = cf.GraphSetC(20, most, 20 * mean, 28 * mean, *([0x1000] * 8))
+    assert cf.lib().cfsim_route_branch(ctypes.byref(s), cf.F32, resize) == branch
+
+
 @pytest.mark.parametrize("dtype,n_a,n_b,max_iter,tol,strips", [
     ("f32", 150, 150, 200, 1e-12, 1), ("f64", 150, 150, 200, 1e-12, 1), ("f32", 333, 410, 200, 1e-3, 1),
     ("f32", 150, 150, 200, 1e-3, 1), ("f32", 150, 150, 1000, 1e-12, 1), ("f32", 150, 150, 4096, 0.0, 1),
