@@ -2014,9 +2014,13 @@ __device__ __forceinline__ void global_pair(const PairJob& J, int p, unsigned ch
     IterOut it;
     if constexpr (MODE == kModePlain && sizeof(T) == 4) {
         // on strips where their tables and two waves' rows fit (the old
-        // workspace of a plain pair holds no tables)
+        // workspace of a plain pair holds no tables), for graphs of up to three
+        // jumps per node: the entries past the slots are a serial chain there.
+        // 276 pairs of 150 nodes, 20 updates, strips against gathers (ms): 3.2
+        // jumps per node 18.9 / 18.3, 4: 27.6 / 20.4, 8: 80.9 / 44.3 (random
+        // graphs; control-flow graphs have 1.4 and gain, see strips.h)
         const int waves = strip_waves<T>(nR, NT / kWave, (size_t)plain_global_lds((int)sizeof(T)));
-        if (J.tabs && waves >= 2 &&
+        if (J.tabs && waves >= 2 && R.nnz + C.nnz <= 3 * (nR + nC) &&
             (long long)((nC + strips::kRows - 1) / strips::kRows) * (long long)sizeof(strips::StripTab<T>) <= J.tab_stride) {
             int pos_r = 0, pos_c = 0;
             for (int t = threadIdx.x; t < R.nnz; t += NT) pos_r |= R.w[t] > 0.0;

@@ -10,7 +10,7 @@ import re
 import numpy as np
 import pytest
 
-from cfgsynth import Grammar, make_cfg
+from cfgsynth import CFG, Grammar, make_cfg
 from tests.parity import check_matching, oracle_pair, rel_err
 from tests.test_gpu_routes import ONE_WORKGROUP, launches
 from tests.test_gpu_strips import _wide
@@ -114,6 +114,24 @@ def test_large_pairs_without_room_for_strips_run_on_the_tiles(cfm, ctx, kind, ma
         assert rel_err(S, ref.S) <= _tol(dtype)
         assert res["iters"][q] == ref.iters and (res["status"][q] & 15) == ref.status
         check_matching(S, match, ref.S, dtype)
+
+
+@pytest.mark.parametrize("jumps", [0, 1, 300])
+def test_batch_pairs_past_lds_around_three_jumps_per_node(cfm, ctx, jumps):
+    # up to three per node on strips, above on gathers
+    rng = np.random.default_rng(jumps)
+    graphs = []
+    for n, extra in ((160, 0), (175, jumps)):
+        m = 3 * n + extra
+        graphs.append(CFG(n, rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32),
+                          rng.integers(1, 100, m).astype(np.float64)))
+    gs = cfm.pack(ctx, graphs)
+    res, match, S = cfm.score_batch(ctx, gs, [0, 1], [1, 0], dtype="f32", max_iter=20, tol=0.0, want_S=True)
+    for q, (a, b) in enumerate([(0, 1), (1, 0)]):
+        ref = oracle_pair(graphs, a, b, max_iter=20, tol=0.0)
+        assert rel_err(S[q], ref.S) <= _tol("f32")
+        assert res["iters"][q] == ref.iters and (res["status"][q] & 15) == ref.status
+        check_matching(S[q], match[q], ref.S, "f32")
 
 
 @pytest.mark.parametrize("dtype,pairs", [("f32", 253), ("f64", 127)])
