@@ -286,8 +286,9 @@ cfsim_status cfsim_score_batch(cfsim_context* ctx, const cfsim_graph_set* set,
  * thousands of nodes): same arguments, outputs and per-pair semantics as
  * cfsim_score_batch, for pairs whose lists do not fit the batched kernels
  * (those report CFSIM_INVALID_INPUT there).  The iterates live in the
- * workspace (HBM); every update is one launch over the strips (resized: the
- * tiles) of all pairs of the call, followed by a per-pair reduction launch; the whole sequence
+ * workspace (HBM); every update is one launch over the strips (resized calls,
+ * and calls of many pairs of smaller graphs: the tiles) of all pairs of the call,
+ * followed by a per-pair reduction launch; the whole sequence
  * (about 2 * max_iter launches, 3 * max_iter with resize) is captured once
  * into a HIP graph cached in the context.  This tiled path also serves every resized pair (opt->resize =
  * CFSIM_RESIZE_BILINEAR) of cfsim_score and cfsim_score_batch.  Limits:

@@ -273,10 +273,6 @@ void append_key(std::vector<unsigned char>& k, const X& x) {
 //   | without resize: strip lists and tables per pair
 int large_nslots(const cfsim_options* o) { return o->resize == CFSIM_RESIZE_BILINEAR ? 6 : 4; }
 
-// Whether plain pairs of a call run on strips (given the room for them).
-bool large_strips(const cfsim_options* o, int max_nodes) {
-    return large_nslots(o) == 4 && !mfma_bf16(o) && cfsim::large_on_strips(max_nodes, esize_of(o->dtype));
-}
 size_t large_part_count(int64_t n_pairs, int max_nodes, bool strips) {
     return (size_t)n_pairs * (size_t)(strips ? cfsim::large_parts(max_nodes) : cfsim::large_tiles(max_nodes));
 }
@@ -1239,12 +1235,40 @@ cfsim_status cfsim_batch_timings(cfsim_context* ctx, float* ms) {
 }
 
 // ------------------------------------------------------------------ large pairs (a9)
+// Whether the plain pairs of a cfsim_score_large call run on strips (given the
+// room for them).  A strip costs 10-20 ns (FP64 20-60) however few of its eight
+// waves have columns, once the launch is full of them, where the tiles' gathers
+// are paid by entry and less for graphs of few jumps: strips win while a launch
+// is bound by latency, and above 384 nodes (FP64 768), by up to four times, and
+// lose calls of many pairs of smaller graphs.  us per update, tiles / strips, for
+// control-flow graphs of 1.37 jumps per node unless said: FP32 64 nodes, 276 pairs
+// 73 / 52, 1,128 pairs 138 / 209; 125 nodes, 276 150 / 111, 1,128 289 / 409; 256
+// nodes, 496 547 / 462; 1.17 jumps, 256 nodes, 66 pairs 52 / 52, 276 184 / 205;
+// chains (1.0 jumps), 400 nodes, 28 pairs 44 / 40, 120 115 / 152.  FP64 125 nodes,
+// 120 pairs 105 / 95, 276 176 / 207; 256 nodes, 66 129 / 122, 276 412 / 530; 400
+// nodes, 66 263 / 222, 276 928 / 1,013; 1,000 nodes, 66 1,196 / 973.
+int cfsim_route_large_strips(const cfsim_graph_set* set, int64_t n_pairs, const cfsim_options* opt) {
+    const int n = set->max_nodes;
+    const bool f64 = opt->dtype == CFSIM_F64;
+    if (large_nslots(opt) != 4 || mfma_bf16(opt) || !cfsim::large_on_strips(n, esize_of(opt->dtype))) return 0;
+    const double jumps = (double)set->total_edges / (double)(set->total_nodes > 0 ? set->total_nodes : 1);
+    double most = f64 ? 4000.0 : 9000.0;  // strips of a launch
+    if (jumps < 1.1) {
+        most = f64 ? 1000.0 : 3000.0;
+    } else {
+        if (n >= (f64 ? 768 : 384) || (!f64 && n >= 192 && jumps >= 1.25)) return 1;
+        if (jumps < 1.25) most *= 0.5;
+        if (f64 && n >= 384) most *= 1.75;
+    }
+    return (double)n_pairs * ((n + 3) / 4) <= most;
+}
+
 size_t cfsim_large_workspace_size(const cfsim_context* ctx, const cfsim_graph_set* set, int64_t n_pairs,
                                   const cfsim_options* opt) {
     (void)ctx;
     if (n_pairs < 1 || !set || !opt || set->max_nodes < 1 || set->max_nodes > cfsim::kLargeMaxNodes) return 0;
     size_t b = large_ws_bytes(n_pairs, set->max_nodes, esize_of(opt->dtype), large_nslots(opt),
-                              large_strips(opt, set->max_nodes));
+                              cfsim_route_large_strips(set, n_pairs, opt) != 0);
     if (mfma_bf16(opt)) b += mfma_ws_bytes(n_pairs, set->max_nodes);
     return b;
 }
@@ -1273,8 +1297,9 @@ cfsim_status cfsim_score_large(cfsim_context* ctx, const cfsim_graph_set* set, c
     // strips with the workspace that the size function names; without the room
     // for their lists the tiles
     const size_t full = cfsim_large_workspace_size(ctx, set, n_pairs, opt);
-    const bool strips = large_strips(opt, set->max_nodes) && ws_bytes >= full;
-    const size_t need = large_strips(opt, set->max_nodes)
+    const bool route = cfsim_route_large_strips(set, n_pairs, opt) != 0;
+    const bool strips = route && ws_bytes >= full;
+    const size_t need = route
                             ? large_ws_bytes(n_pairs, set->max_nodes, esize_of(opt->dtype), 4, false)
                             : full;
     if (ws_bytes < need || !ws) return fail(CFSIM_E_WORKSPACE, "workspace of %zu bytes, %zu needed", ws_bytes, need);

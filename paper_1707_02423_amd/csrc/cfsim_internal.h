@@ -537,6 +537,7 @@ double updates_expected(const cfsim_options* opt);
 extern "C" {
 int cfsim_route_branch(const cfsim_graph_set* set, int dtype, int resize);
 int cfsim_route_score_strips(int n_a, int n_b, const cfsim_options* opt);
+int cfsim_route_large_strips(const cfsim_graph_set* set, int64_t n_pairs, const cfsim_options* opt);
 int cfsim_route_backward_strips(const cfsim_graph_set* set, int64_t n_pairs, const cfsim_options* opt,
                                 int32_t checkpoint_every, int32_t num_cus);
 }

@@ -534,7 +534,8 @@ __global__ __launch_bounds__(kStepThreads) void large_step(LargeJob J, int k) {
 }
 
 // ---------------------------------------------------------------- strips
-// Plain pairs (calls without resize): the iterates are kept as X = S^T, n_A
+// Plain pairs (calls without resize, as cfsim_route_large_strips in api.hip
+// decides): the iterates are kept as X = S^T, n_A
 // rows of n_B entries, and launch k (1 .. max_iter + 1) takes strips of four
 // rows of all pairs (strips.h): source rows read once per strip and added by
 // FP32 matrix instructions, neighbours gathered from LDS.  The terms of an

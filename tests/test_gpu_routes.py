@@ -111,3 +111,25 @@ def test_the_reverses_launches(cfm, ctx):
     assert n([128, 100, 60], 3, "f32", 2000, 0.5, 8) == ONE_WORKGROUP
     assert n([64, 50, 60], 130, "f64", 16, 0.0, 4) == ONE_WORKGROUP
     assert n([400, 420], 2, "f32", 16, 0.0, 4) == ONE_WORKGROUP
+
+
+@pytest.mark.parametrize("dtype,pairs", [("f32", 600), ("f64", 300)])
+def test_many_small_pairs_on_the_large_path(cfm, ctx, dtype, pairs):
+    # past the strips' line: the tiles give what strips give for the first few of them, up to rounding (20 updates of
+    # at most one rounding each, and of the norms)
+    graphs = [make_cfg(n, Grammar(counts="trip"), seed=n) for n in (60, 63, 64, 57)]
+    gs = cfm.pack(ctx, graphs)
+    a, b = (np.tile(x.astype(np.int32), pairs // 6) for x in np.triu_indices(4, 1))
+    L = cfm.lib()
+    out = []
+    for m in (6, pairs):
+        B = cfm.Batch(ctx, gs, a[:m], b[:m], dtype=dtype, max_iter=20, tol=0.0, want_S=True, path="large")
+        assert L.cfsim_route_large_strips(ctypes.byref(B.set_c), ctypes.c_int64(m), ctypes.byref(B.opt)) == (m == 6)
+        B.run()
+        torch.cuda.synchronize()
+        out.append((B.S_list()[:6], B.results()[:6].copy(), B.S_list()[-6:]))
+    for q in range(6):
+        S = out[0][0][q]
+        assert np.abs(S - out[1][0][q]).max() <= (2e-6 if dtype == "f32" else 1e-13) * np.abs(S).max()
+        assert out[0][1]["iters"][q] == out[1][1]["iters"][q] == 20
+        np.testing.assert_array_equal(out[1][0][q], out[1][2][q])

@@ -83,3 +83,25 @@ def test_the_reverse_takes_strips_where_they_pay(dtype, max_nodes, pairs, max_it
     opt = cf.options(dtype, max_iter, tol)
     L = cf.lib()
     assert L.cfsim_route_backward_strips(ctypes.byref(s), ctypes.c_int64(pairs), ctypes.byref(opt), every, 256) == strips
+
+
+@pytest.mark.parametrize("dtype,n,pairs,jumps,strips", [
+    ("f32", 64, 276, 1.37, 1), ("f32", 64, 1128, 1.37, 0), ("f32", 191, 300, 1.37, 0), ("f32", 192, 100000, 1.37, 1),
+    ("f32", 256, 66, 1.2, 1), ("f32", 256, 276, 1.2, 0), ("f32", 400, 100000, 1.2, 1), ("f32", 400, 120, 1.0, 0),
+    ("f32", 2048, 64, 1.37, 1), ("f32", 4992, 2, 1.37, 1), ("f32", 4993, 2, 1.37, 0),
+    ("f64", 125, 120, 1.37, 1), ("f64", 125, 276, 1.37, 0), ("f64", 400, 66, 1.37, 1), ("f64", 400, 120, 1.37, 0),
+    ("f64", 768, 1000, 1.37, 1), ("f64", 256, 28, 1.0, 0), ("f64", 256, 10, 1.0, 1), ("f64", 2496, 1, 1.37, 1),
+    ("f64", 2497, 1, 1.37, 0),
+])
+def test_large_calls_take_strips_or_tiles_by_size(dtype, n, pairs, jumps, strips):
+    s = cf.GraphSetC(20, n, 20 * n, int(20 * n * jumps) + 1, *([0x1000] * 8))
+    L = cf.lib()
+    for kw in (dict(), dict(resize="bilinear"), dict(mfma=True)):
+        if dtype == "f64" and "mfma" in kw:
+            continue
+        opt = cf.options(dtype, **kw)
+        got = L.cfsim_route_large_strips(ctypes.byref(s), ctypes.c_int64(pairs), ctypes.byref(opt))
+        assert got == (strips if not kw else 0)
+    # the workspace is that of the route: tiles need no strip lists
+    size = L.cfsim_large_workspace_size(None, ctypes.byref(s), ctypes.c_int64(pairs), ctypes.byref(cf.options(dtype)))
+    assert size >= pairs * 4 * n * n * (8 if dtype == "f64" else 4)
