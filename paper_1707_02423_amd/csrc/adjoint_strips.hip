@@ -806,6 +806,14 @@ int launch_bwd_strips(int dtype, const BwdJob& J, int max_nodes, int num_cus, hi
 //     8-64 5.9 / 6.4 and one of 12 x 16 1.2 / 1.6.  FP64, 100 of 90-128 22.5 /
 //     12.5, 100 of 60-64 8.7 / 5.9, 64 of 8-48 3.6 / 3.3, but 250 of 90-128 29.9 /
 //     32.3 and of 60-64 10.2 / 12.8.
+//   - of small graphs fewer pairs, 2.2 (n - 28) in FP64 and 5 (n - 24) in FP32
+//     sets of nearly straight code: a strip's cost does not shrink with its columns,
+//     and one workgroup holds such a pair's update in few instructions.  Time of one
+//     workgroup over that of strips, backward of 100 updates: FP64, 20 pairs of 27-33
+//     nodes 0.89-1.01, 48 of 34-40 0.89-1.00 and 128 of them 0.63-0.71, 48 of 42-48
+//     0.94-1.03, 90 of 58-64 1.01-1.08, 128 of 74-80 0.85-0.96, of 90-96 1.01-1.15;
+//     FP32 chains, 128 of 34-40 0.90 and 190 of them 0.82, 128 of 42-48 1.00, 190 of
+//     58-64 0.96; with 1.35 jumps per node 190 of 34-48 0.99-1.00.
 //   - where the set's largest pairs are strips' pairs: else the one-workgroup
 //     kernel, which takes those after the strips, sets the time alone (FP64, 160
 //     pairs of 16-256: 163 / 203).
@@ -824,6 +832,7 @@ extern "C" int cfsim_route_backward_strips(const cfsim_graph_set* set, int64_t n
     if (n < 32 || n > kBwdStripNodes) return 0;
     if (n_pairs < 1 || n_pairs > (f64 ? num_cus / 2 : num_cus) || n_pairs > kMaxPairs) return 0;
     const int nnz = mean_jumps(set, n);
+    if (f64 ? 5 * n_pairs > 11 * (n - 28) : 4 * nnz < 5 * n && n_pairs > 5 * (n - 24)) return 0;
     const BwdShape s = bwd_shape(n, n, nnz, nnz, nnz, f64 ? 8 : 4);
     if (!s.fits || !s.lane_edges) return 0;
     const double every = checkpoint_every < opt->max_iter ? checkpoint_every : opt->max_iter;

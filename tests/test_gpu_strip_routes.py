@@ -134,10 +134,10 @@ def test_batch_pairs_past_lds_around_three_jumps_per_node(cfm, ctx, jumps):
         check_matching(S[q], match[q], ref.S, "f32")
 
 
-@pytest.mark.parametrize("dtype,pairs", [("f32", 253), ("f64", 127)])
-def test_a_reverse_call_of_many_unequal_pairs_on_strips(cfm, ctx, dtype, pairs):
-    # an odd number of pairs over the XCDs, 8 to 48 nodes
-    graphs = [make_cfg(8 + i % 41, Grammar(counts="trip"), seed=i) for i in range(46)]
+@pytest.mark.parametrize("dtype,pairs,step", [("f32", 253, 1), ("f64", 127, 2)])
+def test_a_reverse_call_of_many_unequal_pairs_on_strips(cfm, ctx, dtype, pairs, step):
+    # an odd number of pairs over the XCDs, 8 to 48 (88) nodes
+    graphs = [make_cfg(8 + step * (i % 41), Grammar(counts="trip"), seed=i) for i in range(46)]
     gs = cfm.pack(ctx, graphs)
     a, b = (x.astype(np.int32)[:pairs] for x in np.triu_indices(46))
     weight = torch.linspace(0.5, 1.5, pairs, dtype=torch.float64, device="cuda")

@@ -85,6 +85,18 @@ def test_the_reverse_takes_strips_where_they_pay(dtype, max_nodes, pairs, max_it
     assert L.cfsim_route_backward_strips(ctypes.byref(s), ctypes.c_int64(pairs), ctypes.byref(opt), every, 256) == strips
 
 
+@pytest.mark.parametrize("dtype,max_nodes,pairs,jumps,strips", [
+    ("f64", 40, 26, 1.37, 1), ("f64", 40, 27, 1.37, 0), ("f64", 64, 79, 1.37, 1), ("f64", 64, 80, 1.0, 0),
+    ("f64", 32, 9, 1.37, 0), ("f64", 87, 128, 1.37, 1), ("f32", 40, 80, 1.1, 1), ("f32", 40, 81, 1.1, 0),
+    ("f32", 40, 256, 1.37, 1), ("f32", 76, 256, 1.0, 1), ("f32", 64, 201, 1.0, 0),
+])
+def test_the_reverse_of_small_graphs_takes_strips_for_fewer_pairs(dtype, max_nodes, pairs, jumps, strips):
+    s = cf.GraphSetC(20, max_nodes, 20 * max_nodes, int(20 * max_nodes * jumps) + 1, *([0x1000] * 8))
+    opt = cf.options(dtype, 200, 1e-12)
+    L = cf.lib()
+    assert L.cfsim_route_backward_strips(ctypes.byref(s), ctypes.c_int64(pairs), ctypes.byref(opt), 8, 256) == strips
+
+
 @pytest.mark.parametrize("dtype,n,pairs,jumps,strips", [
     ("f32", 64, 276, 1.37, 1), ("f32", 64, 1128, 1.37, 0), ("f32", 191, 300, 1.37, 0), ("f32", 192, 100000, 1.37, 1),
     ("f32", 256, 66, 1.2, 1), ("f32", 256, 276, 1.2, 0), ("f32", 400, 100000, 1.2, 1), ("f32", 400, 120, 1.0, 0),
